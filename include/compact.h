@@ -127,10 +127,10 @@ typedef enum {
  *   ws, ws_bytes  optional workspace of at least
  *         compact_fwd_workspace_bytes(n, m, r, dtype) bytes (bf16 path).  With
  *         it the call stages W^T and this call's P^T (r x n, P rounded to
- *         bf16 once) in the workspace and runs one persistent GEMM over both
- *         (when n % 8 == 0, n >= 320 and m, r are even; otherwise the fused
- *         GEMM reads the staged P^T and W directly); with ws == NULL the fused
- *         GEMM regenerates every P tile in LDS.  All paths give bitwise
+ *         bf16 once) in the workspace and runs one GEMM over both (a
+ *         persistent one where its tiles fill the GPU, smaller tiles
+ *         elsewhere); with ws == NULL the fused GEMM regenerates every P tile
+ *         in LDS.  All paths give bitwise
  *         identical y and z.  The workspace is scratch: it is dead when the
  *         call's kernels have finished.
  * Requirements: tokens >= 0, n >= 1, m >= 1, 1 <= r <= n.

@@ -22,10 +22,11 @@ INCLUDE = os.path.join(ROOT, "include")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-# Translation units and their extra flags.  The persistent GEMM's K steps are
-# written in issue order, so its unit is compiled with the machine scheduler off.
+# Translation units and their extra flags.  The GEMMs' K steps are written in
+# issue order, so their units are compiled with the machine scheduler off.
 UNITS = [
     ("compact_api.hip", []),
+    ("kernels_tile.hip", ["-mllvm", "-enable-misched=false", "-mllvm", "-enable-post-misched=false"]),
     ("kernels_w4.hip", ["-mllvm", "-enable-misched=false", "-mllvm", "-enable-post-misched=false"]),
 ]
 

@@ -11,6 +11,7 @@
 #include <mutex>
 
 #include "../../include/compact.h"
+#include "gemm_tile.hpp"
 #include "gemm_w4_launch.hpp"
 #include "kernels_bf16.hpp"
 #include "kernels_common.hpp"
@@ -294,6 +295,22 @@ size_t dx_stage_bytes(int64_t n, int64_t m) { return size_t(round_up(n, kW4Tile)
 int w4_tiles(int64_t cols) { return static_cast<int>(ceil_div(cols, kW4Tile)); }
 int64_t n_ld(int64_t m) { return round_up(m, 8); }
 
+W4Seg w4_seg(void* c, int64_t ld, int64_t cols) {
+  return W4Seg{static_cast<uint16_t*>(c), static_cast<int>(ld), static_cast<int>(cols), w4_tiles(cols)};
+}
+
+// Which bf16 GEMM takes a product, given which of them can: kPersistent when
+// the persistent kernel is the better one, or when no tile kernel takes it.
+int choose_gemm(int64_t M, int64_t n0, int64_t n1, int64_t K, bool w4, bool tile, TileKind& kind) {
+  kind = TileKind::kPersistent;
+  if (!tile) return COMPACT_OK;
+  int cus = 0;
+  const hipError_t e = device_cus(&cus);
+  if (e != hipSuccess) return fail(COMPACT_EHIP, "device query: %s", hipGetErrorString(e));
+  kind = gemm_tile_choose(M, n0, n1, K, w4, cus);
+  return COMPACT_OK;
+}
+
 // The projection of a (validated) compact_proj code: kind, rank and, for the
 // sparse projection, the draws per row (0 in the code means the default).
 ProjDesc proj_desc(int proj, int64_t r) {
@@ -430,10 +447,10 @@ struct FwdGroup {
 
 size_t fwd_group_ws_bytes(int64_t n, const FwdGroup& G) { return fwd_ws_bytes(n, G.msum, G.rsum, G.count); }
 
-// The persistent bf16 forward over the stacked operand [W^T; pad to 256;
-// P_0^T; P_1^T; ...]: y in the first column tiles, z after.  Sets `taken`
-// to false (and launches nothing) when the persistent kernel does not take
-// the shape.
+// The bf16 forward over the stacked operand [W^T; pad to 256; P_0^T; P_1^T;
+// ...]: y in the first column tiles, z after.  The operand is staged K-tiled
+// for the persistent kernel, row-major for the tile kernels (gemm_tile_choose).
+// Sets `taken` to false (and launches nothing) when neither takes the shape.
 int fwd_group_w4(const void* x, int64_t ldx, const void* W, int64_t ldw, void* y, int64_t ldy, void* z,
                  int64_t ldz, int64_t tokens, int64_t n, const FwdGroup& G, int proj, void* ws,
                  hipStream_t s, bool& taken) {
@@ -442,9 +459,15 @@ int fwd_group_w4(const void* x, int64_t ldx, const void* W, int64_t ldw, void* y
   // gather-add z: the GEMM computes y alone and its B operand is W^T alone
   const bool gather = proj_gather(proj);
   const int64_t rows_b = gather ? round_up(G.msum, kW4Tile) : stacked_rows(G.msum, G.rsum);
-  taken = ws != nullptr &&
-          gemm_w4_eligible(tokens, n, ldx, ldb, rows_b, ldy, G.msum, gather ? 0 : ldz, gather ? 0 : G.rsum, true) &&
-          tiled_fits(rows_b, n);
+  const bool w4 =
+      gemm_w4_eligible(tokens, n, ldx, ldb, rows_b, ldy, G.msum, gather ? 0 : ldz, gather ? 0 : G.rsum, true) &&
+      tiled_fits(rows_b, n);
+  TileKind kind = TileKind::kPersistent;
+  if ((st = choose_gemm(tokens, G.msum, gather ? 0 : G.rsum, n, w4, gemm_tile_eligible(tokens, n, ldx, ldb, rows_b),
+                        kind)))
+    return st;
+  const bool tile = kind != TileKind::kPersistent;
+  taken = ws != nullptr && (tile || w4);
   if (!taken) return COMPACT_OK;
   uint16_t* bs = static_cast<uint16_t*>(align_ws(ws));
   const int64_t mp = round_up(G.msum, kW4Tile);
@@ -452,7 +475,7 @@ int fwd_group_w4(const void* x, int64_t ldx, const void* W, int64_t ldw, void* y
   char* tables = reinterpret_cast<char*>(bs) + round_up(rows_b * ldb * int64_t(sizeof(uint16_t)), int64_t(kWsAlign));
   FwdStage fs{};
   fs.W = static_cast<const uint16_t*>(W); fs.ldw = ldw; fs.n = n; fs.m = G.msum;
-  fs.b = PanelOut{bs, ldb, rows_b}; fs.ldb = ldb;
+  fs.b = PanelOut{bs, ldb, tile ? 0 : rows_b}; fs.ldb = ldb;
   fs.count = G.count;
   fs.kind = proj_desc(proj, 1).kind;
   fs.sparse_s = proj_desc(proj, 1).s;
@@ -476,18 +499,28 @@ int fwd_group_w4(const void* x, int64_t ldx, const void* W, int64_t ldw, void* y
   if (stage_blocks > 0x7FFFFFFF) return fail(COMPACT_EUNSUPPORTED, "staging grid too large");
   hipLaunchKernelGGL(k_fwd_stage_bf16, dim3(static_cast<uint32_t>(stage_blocks)), dim3(256), 0, s, fs);
   if ((st = check_launch("W^T and P^T staging (bf16)"))) return st;
-  W4Gemm g{};
-  g.A = static_cast<const uint16_t*>(x); g.lda = static_cast<int>(ldx);
-  g.M = static_cast<int>(tokens); g.K = static_cast<int>(n);
-  g.B = bs; g.ldb = static_cast<int>(ldb); g.rows_b = static_cast<int>(rows_b); g.b_tiled = 1;
-  g.seg[0] = W4Seg{static_cast<uint16_t*>(y), static_cast<int>(ldy), static_cast<int>(G.msum), w4_tiles(G.msum)};
-  if (!gather)
-    g.seg[1] = W4Seg{static_cast<uint16_t*>(z), static_cast<int>(ldz), static_cast<int>(G.rsum), w4_tiles(G.rsum)};
-  g.tiles_n = g.seg[0].tiles + g.seg[1].tiles;
-  const int64_t tiles = ceil_div(tokens, kW4Tile) * g.tiles_n;
-  if (tiles > 0x7FFFFFFF) return fail(COMPACT_EUNSUPPORTED, "grid too large");
-  g.tiles = static_cast<int>(tiles);
-  const hipError_t e = gemm_w4_launch(g, W4Use::kForward, s);
+  const W4Seg seg_y = w4_seg(y, ldy, G.msum);
+  const W4Seg seg_z = gather ? W4Seg{} : w4_seg(z, ldz, G.rsum);
+  hipError_t e;
+  if (tile) {
+    TGemm g{};
+    g.A = static_cast<const uint16_t*>(x); g.lda = static_cast<int>(ldx);
+    g.M = static_cast<int>(tokens); g.K = static_cast<int>(n);
+    g.B = bs; g.ldb = static_cast<int>(ldb); g.rows_b = static_cast<int>(rows_b); g.b_row1 = static_cast<int>(mp);
+    g.seg[0] = seg_y; g.seg[1] = seg_z;
+    e = gemm_tile_launch(g, kind, s);
+  } else {
+    W4Gemm g{};
+    g.A = static_cast<const uint16_t*>(x); g.lda = static_cast<int>(ldx);
+    g.M = static_cast<int>(tokens); g.K = static_cast<int>(n);
+    g.B = bs; g.ldb = static_cast<int>(ldb); g.rows_b = static_cast<int>(rows_b); g.b_tiled = 1;
+    g.seg[0] = seg_y; g.seg[1] = seg_z;
+    g.tiles_n = g.seg[0].tiles + g.seg[1].tiles;
+    const int64_t tiles = ceil_div(tokens, kW4Tile) * g.tiles_n;
+    if (tiles > 0x7FFFFFFF) return fail(COMPACT_EUNSUPPORTED, "grid too large");
+    g.tiles = static_cast<int>(tiles);
+    e = gemm_w4_launch(g, W4Use::kForward, s);
+  }
   if (e != hipSuccess) return fail(COMPACT_EHIP, "forward GEMM (bf16): %s", hipGetErrorString(e));
   if (!gather) return COMPACT_OK;
   GatherParams gp{};
@@ -701,7 +734,21 @@ int bwd_impl(const void* dy, int64_t lddy, const void* W, int64_t ldw, const voi
 
   const int64_t npad = round_up(n, kW4Tile);
   const bool stage_w = ws != nullptr && ws_bytes >= dx_stage_bytes(n, m) + kWsAlign && tiled_fits(npad, m);
-  if (dx != nullptr && gemm_w4_eligible(tokens, m, lddy, ldw, n, lddx, n, 0, 0, stage_w)) {
+  const bool w4 = gemm_w4_eligible(tokens, m, lddy, ldw, n, lddx, n, 0, 0, stage_w);
+  TileKind kind = TileKind::kPersistent;
+  if (dx != nullptr &&
+      (st = choose_gemm(tokens, n, 0, m, w4, gemm_tile_eligible(tokens, m, lddy, ldw, n), kind)))
+    return st;
+  if (dx != nullptr && kind != TileKind::kPersistent) {
+    // a tile kernel reads W [n][m] as it is: one launch, no copy of W
+    TGemm g{};
+    g.A = static_cast<const uint16_t*>(dy); g.lda = static_cast<int>(lddy);
+    g.M = static_cast<int>(tokens); g.K = static_cast<int>(m);
+    g.B = static_cast<const uint16_t*>(W); g.ldb = static_cast<int>(ldw); g.rows_b = static_cast<int>(n);
+    g.seg[0] = w4_seg(dx, lddx, n);
+    const hipError_t e = gemm_tile_launch(g, kind, s);
+    if (e != hipSuccess) return fail(COMPACT_EHIP, "dx GEMM (bf16): %s", hipGetErrorString(e));
+  } else if (dx != nullptr && w4) {
     // persistent GEMM: dx = dL/do W^T with W [n][m] as the K-contiguous B,
     // copied into the K-tiled layout first when the workspace holds it
     // (always when m % 8 != 0: the copy is zero past m)
@@ -717,8 +764,8 @@ int bwd_impl(const void* dy, int64_t lddy, const void* W, int64_t ldw, const voi
       if ((st = check_launch("W K-tile staging (bf16)"))) return st;
       g.B = wt; g.rows_b = static_cast<int>(npad); g.b_tiled = 1;
     }
-    g.seg[0] = W4Seg{static_cast<uint16_t*>(dx), static_cast<int>(lddx), static_cast<int>(n), w4_tiles(n)};
-    g.seg[1] = W4Seg{static_cast<uint16_t*>(dx), static_cast<int>(lddx), 0, 0};
+    g.seg[0] = w4_seg(dx, lddx, n);
+    g.seg[1] = w4_seg(dx, lddx, 0);
     g.tiles_n = g.seg[0].tiles;
     const int64_t tiles = ceil_div(tokens, kW4Tile) * g.tiles_n;
     if (tiles > 0x7FFFFFFF) return fail(COMPACT_EUNSUPPORTED, "grid too large");
