@@ -11,6 +11,7 @@
 #include <mutex>
 
 #include "../../include/compact.h"
+#include "gemm_f32.hpp"
 #include "gemm_tile.hpp"
 #include "gemm_w4_launch.hpp"
 #include "kernels_bf16.hpp"
@@ -358,6 +359,85 @@ int launch_gemm_f32(const GemmF32Params& gp, hipStream_t s, const char* what) {
   return check_launch(what);
 }
 
+// The MFMA fp32 GEMMs (gemm_f32.hpp) take leading dimensions whose 64-row tiles
+// fit 32-bit buffer offsets; wider ones (rows of 16 MB and more) go through the
+// plain kernel.
+bool f32_fits(std::initializer_list<int64_t> lds) {
+  for (int64_t ld : lds)
+    if (ld >= int64_t(1) << 22) return false;
+  return true;
+}
+
+MatF32 f32_mat(const void* p, int64_t ld, int64_t rows) {
+  MatF32 o{};
+  o.p = static_cast<const float*>(p);
+  o.ld = ld;
+  o.rows = rows;
+  return o;
+}
+
+MatF32 f32_pgen(uint64_t seed, int64_t n, int64_t r, int proj) {
+  MatF32 o{};
+  o.proj = proj_desc(proj, r);
+  o.key = philox_key(seed);
+  o.n = n;
+  return o;
+}
+
+JobF32 f32_job(const MatF32& A, const MatF32& B, int64_t M, int64_t N, int64_t K, void* out, int64_t ldo, float scale,
+               int mode) {
+  JobF32 j{};
+  j.A = A; j.B = B; j.M = M; j.N = N; j.K = K;
+  j.out = static_cast<float*>(out); j.ldo = ldo; j.scale = scale; j.mode = mode;
+  return j;
+}
+
+// One launch over the tiles (Sh0, Sh1) of up to two products; a product with no
+// output has none.
+template <class Sh0, class Sh1>
+int launch_f32_tiles(void (*fn)(PairF32), PairF32 p, hipStream_t s, const char* what) {
+  const int bm[2] = {Sh0::kBM, Sh1::kBM}, bn[2] = {Sh0::kBN, Sh1::kBN};
+  int64_t blocks = 0;
+  for (int k = 0; k < 2; ++k) {
+    JobF32& j = p.job[k];
+    const int64_t tm = j.out != nullptr ? ceil_div(j.M, bm[k]) : 0, tc = ceil_div(j.N, bn[k]);
+    if (tm * tc > 0x7FFFFFFF) return fail(COMPACT_EUNSUPPORTED, "%s: grid too large", what);
+    j.tiles_n = static_cast<int>(tc);
+    j.tiles = static_cast<int>(tm * tc);
+    blocks += j.tiles;
+  }
+  if (blocks == 0) return COMPACT_OK;
+  if (blocks > 0x7FFFFFFF) return fail(COMPACT_EUNSUPPORTED, "%s: grid too large", what);
+  const size_t lds = std::max(Sh0::kLds, Sh1::kLds);
+  int st;
+  if ((st = set_lds(reinterpret_cast<const void*>(fn), lds))) return st;
+  hipLaunchKernelGGL(fn, dim3(static_cast<uint32_t>(blocks)), dim3(256), lds, s, p);
+  return check_launch(what);
+}
+
+// Up to two products, with the kernel's variant for large ones (tiles Sh0, Sh1)
+// or for small ones (Sm0, Sm1): one launch when both are of a kind, else one each
+// (in one launch, the few long tiles of a small product would run as large ones).
+template <class Sh0, class Sh1, class Sm0, class Sm1>
+int launch_f32(void (*fn)(PairF32), void (*fn_small)(PairF32), const PairF32& p, hipStream_t s, const char* what) {
+  int cus = 0;
+  const hipError_t e = device_cus(&cus);
+  if (e != hipSuccess) return fail(COMPACT_EHIP, "%s: %s", what, hipGetErrorString(e));
+  int64_t work[2];
+  for (int k = 0; k < 2; ++k)
+    work[k] = p.job[k].out != nullptr ? ceil_div(p.job[k].M, 64) * ceil_div(p.job[k].N, 64) : 0;
+  if (4 * (work[0] + work[1]) < 3 * int64_t(cus)) return launch_f32_tiles<Sm0, Sm1>(fn_small, p, s, what);
+  const bool small1 = work[1] != 0 && 4 * work[1] < 3 * int64_t(cus) && p.job[1].K >= 512;
+  if (!small1) return launch_f32_tiles<Sh0, Sh1>(fn, p, s, what);
+  PairF32 one = p;
+  one.job[1] = JobF32{};
+  int st;
+  if ((st = launch_f32_tiles<Sh0, Sh1>(fn, one, s, what))) return st;
+  one = p;
+  one.job[0] = JobF32{};
+  return launch_f32_tiles<Sm0, Sm1>(fn_small, one, s, what);
+}
+
 OperandF32 mem_operand(const float* p, int64_t su, int64_t sv, int64_t U, int64_t V) {
   OperandF32 o{};
   o.p = p;
@@ -559,6 +639,13 @@ int compact_fwd(const void* x, int64_t ldx, const void* W, int64_t ldw, void* y,
   if (tokens == 0) return ok();
   hipStream_t s = static_cast<hipStream_t>(stream);
 
+  if (dtype == COMPACT_F32 && f32_fits({ldx, ldw})) {
+    PairF32 p{};
+    p.job[0] = f32_job(f32_mat(x, ldx, tokens), f32_mat(W, ldw, m), tokens, m, n, y, ldy, 1.0f, 0);
+    p.job[1] = f32_job(p.job[0].A, f32_pgen(seed, n, r, proj), tokens, r, n, z, ldz, proj_scale(proj, r), 0);
+    if ((st = launch_f32<F32Big, F32Tall, F32Small, F32Small>(k_fwd_f32<false>, k_fwd_f32<true>, p, s, "forward (fp32)"))) return st;
+    return ok();
+  }
   if (dtype == COMPACT_F32) {
     GemmF32Params gp{};
     gp.A = mem_operand(static_cast<const float*>(x), ldx, 1, tokens, n);
@@ -712,6 +799,15 @@ int bwd_impl(const void* dy, int64_t lddy, const void* W, int64_t ldw, const voi
     return ok();
   }
 
+  if (dtype == COMPACT_F32 && f32_fits({lddy, dx != nullptr ? ldw : 0, G != nullptr ? ldz : 0})) {
+    PairF32 p{};
+    if (dx != nullptr)
+      p.job[0] = f32_job(f32_mat(dy, lddy, tokens), f32_mat(W, ldw, n), tokens, n, m, dx, lddx, 1.0f, 0);
+    if (G != nullptr)
+      p.job[1] = f32_job(f32_mat(z, ldz, r), f32_mat(dy, lddy, m), r, m, tokens, G, m, 1.0f, accumulate ? 2 : 0);
+    if ((st = launch_f32<F32Big, F32Big, F32Small, F32Small>(k_bwd_f32<false>, k_bwd_f32<true>, p, s, "backward (fp32)"))) return st;
+    return ok();
+  }
   if (dtype == COMPACT_F32) {
     if (dx != nullptr) {
       GemmF32Params gp{};
@@ -1040,7 +1136,12 @@ int compact_step(void* W, int64_t ldw, const float* G, float* M, float* V, int64
   std::vector<StepPlan> plans(1);
   plan_step(W, ldw, G, M, V, n, m, r, seed, lr, alpha, proj, dtype, align_ws(ws), plans[0]);
   if ((st = launch_step_groups(plans, adam_consts(t, beta1, beta2, eps, proj, dtype), dtype, w_dtype, s))) return st;
-  if (dtype == COMPACT_F32) {
+  if (dtype == COMPACT_F32 && f32_fits({plans[0].al.ldn})) {
+    PairF32 p{};
+    p.job[0] = f32_job(f32_pgen(seed, n, r, proj), f32_mat(plans[0].al.N, plans[0].al.ldn, m), n, m, r, W, ldw,
+                       plans[0].dl.coef, 1);
+    if ((st = launch_f32<F32Wide, F32Wide, F32Narrow, F32Narrow>(k_dec_f32<false>, k_dec_f32<true>, p, s, "decompress (fp32)"))) return st;
+  } else if (dtype == COMPACT_F32) {
     GemmF32Params gp{};
     gp.A = pgen_operand(seed, n, r, proj);
     gp.B = mem_operand(static_cast<const float*>(plans[0].al.N), plans[0].al.ldn, 1, r, m);

@@ -153,12 +153,12 @@ __device__ __forceinline__ void pstream_angle(uint32_t b, float& ct, float& st) 
   pstream_sincos(x, sx, cx);
   const float s_psi = h ? cx : sx;
   const float c_psi = h ? sx : cx;
-  switch (q) {
-    case 0: ct = c_psi;  st = s_psi;  break;
-    case 1: ct = -s_psi; st = c_psi;  break;
-    case 2: ct = -c_psi; st = -s_psi; break;
-    default: ct = s_psi; st = -c_psi; break;
-  }
+  // rotation by the quadrant, (c, s), (-s, c), (-c, -s), (s, -c), as a swap and
+  // two sign flips: a switch runs all four of its arms with lanes masked off
+  const uint32_t ca = __float_as_uint((q & 1u) != 0u ? s_psi : c_psi);
+  const uint32_t sa = __float_as_uint((q & 1u) != 0u ? c_psi : s_psi);
+  ct = __uint_as_float(ca ^ (((q + 1u) & 2u) << 30));
+  st = __uint_as_float(sa ^ ((q & 2u) << 30));
 }
 
 __device__ __forceinline__ void pstream_pair(uint32_t a, uint32_t b, float& g_even,
