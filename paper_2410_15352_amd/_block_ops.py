@@ -1,0 +1,283 @@
+"""Autograd functions over the block kernels of libcompact.so (csrc/block_ops.hip):
+RMSNorm with its residual, SwiGLU and the mean cross-entropy.
+
+They take dense bf16 tensors on the current GPU; `usable` says whether a call may
+go that way.  Everything else (CPU, other types and strides, tracing, functorch,
+forward-mode AD) takes the torch expressions beside each function, and so does a
+backward that is itself recorded (create_graph=True)."""
+from __future__ import annotations
+
+import ctypes
+
+import torch
+
+from . import _lib
+
+_vp, _i64, _i32, _f32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_float
+RMSNORM_MAX_D = 4096
+IGNORE = -100  # F.cross_entropy's default ignore_index
+
+
+class _NormArgs(ctypes.Structure):
+    _fields_ = [("x", _vp), ("add", _vp), ("g", _vp), ("sum", _vp), ("y", _vp), ("rstd", _vp), ("rows", _i64),
+                ("d", _i32), ("eps", _f32)]
+
+
+class _NormGradArgs(ctypes.Structure):
+    _fields_ = [("x", _vp), ("dy", _vp), ("dres", _vp), ("g", _vp), ("rstd", _vp), ("dx", _vp), ("part", _vp),
+                ("dg", _vp), ("rows", _i64), ("d", _i32)]
+
+
+class _CeArgs(ctypes.Structure):
+    _fields_ = [("x", _vp), ("target", _vp), ("lse", _vp), ("loss_row", _vp), ("loss", _vp), ("count", _vp), ("rows", _i64),
+                ("V", _i64), ("ignore_index", _i64)]
+
+
+class _CeGradArgs(ctypes.Structure):
+    _fields_ = [("x", _vp), ("target", _vp), ("lse", _vp), ("count", _vp), ("dloss", _vp), ("dx", _vp), ("rows", _i64),
+                ("V", _i64), ("ignore_index", _i64)]
+
+
+_SIGNATURES = {
+    "compact_block_rmsnorm_fwd": [ctypes.POINTER(_NormArgs), _vp],
+    "compact_block_rmsnorm_parts": [_i64],
+    "compact_block_rmsnorm_bwd": [ctypes.POINTER(_NormGradArgs), _vp],
+    "compact_block_swiglu_fwd": [_vp, _vp, _vp, _i64, _i64, _vp],
+    "compact_block_swiglu_bwd": [_vp, _vp, _vp, _vp, _i64, _i64, _vp],
+    "compact_block_join3": [_vp, _vp, _vp, _vp, _i64, _i64, _vp],
+    "compact_block_ce_fwd": [ctypes.POINTER(_CeArgs), _vp],
+    "compact_block_ce_bwd": [ctypes.POINTER(_CeGradArgs), _vp],
+}
+_fns = {}
+
+
+def _call(name, *args):
+    fn = _fns.get(name)
+    if fn is None:
+        fn = getattr(_lib.load(), name)
+        fn.restype, fn.argtypes = ctypes.c_int, _SIGNATURES[name]
+        _fns[name] = fn
+    rc = fn(*args)
+    if rc < 0:
+        raise RuntimeError(f"{name}: status {rc}")
+    return rc
+
+
+def _stream(t):
+    return torch.cuda.current_stream(t.device).cuda_stream
+
+
+def _plain(t):
+    return type(t) in (torch.Tensor, torch.nn.Parameter)
+
+
+def usable(*tensors):
+    """Dense bf16 tensors on the current device, outside every kind of tracing."""
+    if torch.compiler.is_compiling() or torch.jit.is_tracing() or torch._C._len_torch_dispatch_stack() > 0:
+        return False
+    if torch._C._functorch.peek_interpreter_stack() is not None or torch.autograd.forward_ad._current_level >= 0:
+        return False
+    for t in tensors:
+        if not (_plain(t) and t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.numel() > 0
+                and t.data_ptr() % 16 == 0):
+            return False
+    return all(t.device.index == torch.cuda.current_device() for t in tensors)
+
+
+def norm_usable(x, g, *rest):
+    return x.dim() >= 1 and x.shape[-1] % 8 == 0 and 8 <= x.shape[-1] <= RMSNORM_MAX_D and usable(x, g, *rest)
+
+
+def _grad(t):
+    """A gradient as the kernels take it."""
+    t = t if t.dtype == torch.bfloat16 else t.to(torch.bfloat16)
+    t = t.contiguous()
+    return t if t.data_ptr() % 16 == 0 else t.clone()
+
+
+# ------------------------------- RMSNorm -----------------------------------
+
+def rmsnorm_reference_grad(x, rstd, g, dy):
+    xhat = x.float() * rstd.unsqueeze(-1)
+    dyf = dy.float()
+    gdy = dyf * g.float()
+    dx = rstd.unsqueeze(-1) * (gdy - xhat * (gdy * xhat).mean(-1, keepdim=True))
+    dg = (dyf * xhat).reshape(-1, x.shape[-1]).sum(0)
+    return dx.to(x.dtype), dg.to(g.dtype)
+
+
+class _NormFn(torch.autograd.Function):
+    """(x, y) with y = x / rms(x) * g, or with `add` (x + add, its norm): the first
+    result carries the residual, so that its gradient and the norm's meet in one
+    kernel.  Saves the normalised tensor and 1 / rms only."""
+
+    @staticmethod
+    def forward(ctx, x, add, g, eps):
+        d = x.shape[-1]
+        rows = x.numel() // d
+        y = torch.empty_like(x)
+        rstd = torch.empty(x.shape[:-1], dtype=torch.float32, device=x.device)
+        total = torch.empty_like(x) if add is not None else None
+        _call("compact_block_rmsnorm_fwd",
+              ctypes.byref(_NormArgs(x.data_ptr(), None if add is None else add.data_ptr(), g.data_ptr(),
+                                     None if add is None else total.data_ptr(), y.data_ptr(), rstd.data_ptr(), rows, d,
+                                     eps)), _stream(x))
+        ctx.set_materialize_grads(False)
+        ctx.added = add is not None
+        ctx.save_for_backward(x if add is None else total, rstd, g)
+        return (x if add is None else total), y
+
+    @staticmethod
+    def backward(ctx, dres, dy):
+        x, rstd, g = ctx.saved_tensors
+        if dy is None:
+            return dres, dres if ctx.added else None, None, None
+        if torch.is_grad_enabled():
+            dx, dg = rmsnorm_reference_grad(x, rstd, g, dy)
+            dx = dx if dres is None else dx + dres
+            return dx, dx if ctx.added else None, dg, None
+        d = x.shape[-1]
+        rows = x.numel() // d
+        dy = _grad(dy)
+        dres = None if dres is None else _grad(dres)
+        need = ctx.needs_input_grad[0] or ctx.needs_input_grad[1]
+        dx = torch.empty_like(x) if need else None
+        dg = torch.empty_like(g)
+        part = torch.empty(_call("compact_block_rmsnorm_parts", rows), d, dtype=torch.float32, device=x.device)
+        _call("compact_block_rmsnorm_bwd",
+              ctypes.byref(_NormGradArgs(x.data_ptr(), dy.data_ptr(), None if dres is None else dres.data_ptr(),
+                                         g.data_ptr(), rstd.data_ptr(), None if dx is None else dx.data_ptr(),
+                                         part.data_ptr(), dg.data_ptr(), rows, d)), _stream(x))
+        return dx, dx if ctx.added else None, dg, None
+
+
+def rmsnorm(x, g, eps):
+    """y alone."""
+    return _NormFn.apply(x, None, g, eps)[1]
+
+
+def rmsnorm_residual(x, g, eps):
+    """(x, y): use the returned x for the residual."""
+    return _NormFn.apply(x, None, g, eps)
+
+
+def add_rmsnorm(x, add, g, eps):
+    """(x + add, its norm)."""
+    return _NormFn.apply(x, add, g, eps)
+
+
+# -------------------------------- SwiGLU -----------------------------------
+
+class _SwigluFn(torch.autograd.Function):
+    """silu(gate) * up of gu = [gate | up]; keeps gu and silu(gate)."""
+
+    @staticmethod
+    def forward(ctx, gu):
+        rows, f = gu.shape[0], gu.shape[1] // 2
+        s = torch.empty(rows, f, dtype=gu.dtype, device=gu.device)
+        act = torch.empty_like(s)
+        _call("compact_block_swiglu_fwd", gu.data_ptr(), s.data_ptr(), act.data_ptr(), rows, f, _stream(gu))
+        ctx.save_for_backward(gu, s)
+        return act
+
+    @staticmethod
+    def backward(ctx, dact):
+        gu, s = ctx.saved_tensors
+        rows, f = s.shape
+        if torch.is_grad_enabled():
+            g, u = gu[:, :f], gu[:, f:]
+            sg = torch.sigmoid(g.float())
+            dg = dact.float() * u.float() * (sg * (1 + g.float() * (1 - sg)))
+            return torch.cat([dg.to(gu.dtype), dact * torch.nn.functional.silu(g)], 1)
+        dact = _grad(dact)
+        dgu = torch.empty_like(gu)
+        _call("compact_block_swiglu_bwd", gu.data_ptr(), s.data_ptr(), dact.data_ptr(), dgu.data_ptr(), rows, f,
+              _stream(gu))
+        return dgu
+
+
+def swiglu(gu, f):
+    """silu(gu[:, :f]) * gu[:, f:]."""
+    if gu.dim() == 2 and gu.shape[1] == 2 * f and f % 8 == 0 and usable(gu):
+        return _SwigluFn.apply(gu)
+    return torch.nn.functional.silu(gu[:, :f]) * gu[:, f:]
+
+
+# ------------------------------ q, k, v -------------------------------------
+
+class _SplitQkvFn(torch.autograd.Function):
+    """q, k, v (b, heads, l, hd) as views of qkv (b, l, 3, heads, hd); the backward
+    joins their gradients in one pass when each is dense as (b, l, heads, hd), the
+    layout attention's backward gives them."""
+
+    @staticmethod
+    def forward(ctx, qkv):
+        ctx.shape = qkv.shape
+        ctx.set_materialize_grads(False)
+        return tuple(t.transpose(1, 2) for t in qkv.unbind(2))
+
+    @staticmethod
+    def backward(ctx, *grads):
+        b, l, _, heads, hd = ctx.shape
+        if any(g is None for g in grads):
+            some = next((g for g in grads if g is not None), None)
+            if some is None:
+                return None
+            grads = [torch.zeros_like(some) if g is None else g for g in grads]
+        grads = [g.transpose(1, 2) for g in grads]
+        d = heads * hd
+        if torch.is_grad_enabled() or d % 8 != 0 or not usable(*grads):
+            return torch.stack(grads, 2)
+        out = torch.empty(ctx.shape, dtype=grads[0].dtype, device=grads[0].device)
+        _call("compact_block_join3", *(g.data_ptr() for g in grads), out.data_ptr(), b * l, d, _stream(out))
+        return out
+
+
+def split_qkv(qkv):
+    """q, k, v (b, heads, l, hd) of qkv (b, l, 3, heads, hd)."""
+    if usable(qkv):
+        return _SplitQkvFn.apply(qkv)
+    return tuple(t.transpose(1, 2) for t in qkv.unbind(2))
+
+
+# ----------------------------- cross-entropy --------------------------------
+
+class _CrossEntropyFn(torch.autograd.Function):
+    """Mean cross-entropy of bf16 logits (rows, V), in fp32; keeps the logits and
+    one log-sum-exp per row."""
+
+    @staticmethod
+    def forward(ctx, logits, targets):
+        rows, V = logits.shape
+        lse = torch.empty(rows + 1, dtype=torch.float32, device=logits.device)  # and the count
+        loss_row = torch.empty(rows, dtype=torch.float32, device=logits.device)
+        loss = torch.empty((), dtype=torch.float32, device=logits.device)
+        _call("compact_block_ce_fwd",
+              ctypes.byref(_CeArgs(logits.data_ptr(), targets.data_ptr(), lse.data_ptr(), loss_row.data_ptr(),
+                                   loss.data_ptr(), lse.data_ptr() + 4 * rows, rows, V, IGNORE)), _stream(logits))
+        ctx.save_for_backward(logits, targets, lse)
+        return loss
+
+    @staticmethod
+    def backward(ctx, dloss):
+        logits, targets, lse = ctx.saved_tensors
+        rows, V = logits.shape
+        if torch.is_grad_enabled():
+            keep = targets != IGNORE
+            p = torch.softmax(logits.float(), -1)
+            p = p - torch.nn.functional.one_hot(targets.clamp(min=0), V)
+            return (p * (keep.float() * dloss / lse[rows]).unsqueeze(-1)).to(logits.dtype), None
+        dloss = dloss.float().contiguous()
+        dx = torch.empty_like(logits)
+        _call("compact_block_ce_bwd",
+              ctypes.byref(_CeGradArgs(logits.data_ptr(), targets.data_ptr(), lse.data_ptr(),
+                                       lse.data_ptr() + 4 * rows, dloss.data_ptr(), dx.data_ptr(), rows, V, IGNORE)), _stream(logits))
+        return dx, None
+
+
+def cross_entropy(logits, targets):
+    """F.cross_entropy(logits.float(), targets) for 2-D logits and class targets."""
+    if (logits.dim() == 2 and _plain(targets) and targets.dtype == torch.int64 and targets.dim() == 1
+            and targets.shape[0] == logits.shape[0] and targets.device == logits.device and usable(logits)):
+        return _CrossEntropyFn.apply(logits, targets.contiguous())
+    return torch.nn.functional.cross_entropy(logits.float(), targets)

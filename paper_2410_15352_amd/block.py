@@ -21,6 +21,7 @@ from __future__ import annotations
 import torch
 from torch.nn.attention import SDPBackend, sdpa_kernel
 
+from . import _block_ops as ops
 from .nn import CompActAdam, CompActGroup, CompActLinear
 
 __all__ = ["RMSNorm", "DenseLinear", "LlamaBlock", "LlamaModel", "block_saved_bytes", "make_optimizers"]
@@ -31,7 +32,8 @@ def _pad8(c):
 
 
 class _RMSNormFn(torch.autograd.Function):
-    """y = x / rms(x) * g over the last dimension, saving x and 1/rms only."""
+    """y = x / rms(x) * g over the last dimension, saving x and 1/rms only (the
+    torch expressions, where the block kernels do not apply)."""
 
     @staticmethod
     def forward(ctx, x, g, eps):
@@ -43,12 +45,8 @@ class _RMSNormFn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dy):
         x, rstd, g = ctx.saved_tensors
-        xhat = x.float() * rstd.unsqueeze(-1)
-        dyf = dy.float()
-        gdy = dyf * g.float()
-        dx = rstd.unsqueeze(-1) * (gdy - xhat * (gdy * xhat).mean(-1, keepdim=True))
-        dg = (dyf * xhat).reshape(-1, x.shape[-1]).sum(0)
-        return dx.to(x.dtype), dg.to(g.dtype), None
+        dx, dg = ops.rmsnorm_reference_grad(x, rstd, g, dy)
+        return dx, dg, None
 
 
 class RMSNorm(torch.nn.Module):
@@ -58,7 +56,23 @@ class RMSNorm(torch.nn.Module):
         self.eps = eps
 
     def forward(self, x):
+        if ops.norm_usable(x, self.weight):
+            return ops.rmsnorm(x, self.weight, self.eps)
         return _RMSNormFn.apply(x, self.weight, self.eps)
+
+    def with_residual(self, x):
+        """(x, norm(x)); the returned x is the one to add to later, so that both
+        gradients of x are summed where the norm's is formed."""
+        if ops.norm_usable(x, self.weight):
+            return ops.rmsnorm_residual(x, self.weight, self.eps)
+        return x, _RMSNormFn.apply(x, self.weight, self.eps)
+
+    def add(self, x, o):
+        """(x + o, norm(x + o))."""
+        if x.shape == o.shape and ops.norm_usable(x, self.weight, o):
+            return ops.add_rmsnorm(x, o, self.weight, self.eps)
+        s = x + o
+        return s, _RMSNormFn.apply(s, self.weight, self.eps)
 
 
 class DenseLinear(torch.nn.Module):
@@ -110,16 +124,16 @@ class LlamaBlock(torch.nn.Module):
 
     def forward(self, x):
         b, l, d = x.shape
-        h = self.norm1(x)
+        x, h = self.norm1.with_residual(x)
         qkv = self.qkv(h.reshape(b * l, d)).reshape(b, l, 3, self.heads, d // self.heads)
-        q, k, v = (qkv[:, :, i].transpose(1, 2) for i in range(3))
+        # (three slices would each scatter into a zero-filled tensor of q|k|v's size
+        # in the backward, which are then summed)
+        q, k, v = ops.split_qkv(qkv)
         with sdpa_kernel([SDPBackend.FLASH_ATTENTION]):
             a = torch.nn.functional.scaled_dot_product_attention(q, k, v, is_causal=True)
-        x5 = x + self.o(a.transpose(1, 2).reshape(b * l, d)).reshape(b, l, d)
-        h2 = self.norm2(x5)
+        x5, h2 = self.norm2.add(x, self.o(a.transpose(1, 2).reshape(b * l, d)).reshape(b, l, d))
         gu = self.gu(h2.reshape(b * l, d))
-        act = torch.nn.functional.silu(gu[:, :self.ffn]) * gu[:, self.ffn:]
-        return x5 + self.down(act).reshape(b, l, d)
+        return x5 + self.down(ops.swiglu(gu, self.ffn)).reshape(b, l, d)
 
     def compact_modules(self):
         return [m for m in (self.qkv, self.o, self.gu, self.down) if isinstance(m, CompActGroup)]
@@ -167,7 +181,7 @@ class LlamaModel(torch.nn.Module):
         for blk in self.blocks:
             x = blk(x)
         logits = self.head(self.norm(x))
-        return torch.nn.functional.cross_entropy(logits.reshape(-1, logits.shape[-1]).float(), targets.reshape(-1))
+        return ops.cross_entropy(logits.reshape(-1, logits.shape[-1]), targets.reshape(-1))
 
     def compact_modules(self):
         return [m for blk in self.blocks for m in blk.compact_modules()]

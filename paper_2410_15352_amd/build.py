@@ -26,6 +26,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # issue order, so their units are compiled with the machine scheduler off.
 UNITS = [
     ("compact_api.hip", []),
+    ("block_ops.hip", []),
     ("kernels_tile.hip", ["-mllvm", "-enable-misched=false", "-mllvm", "-enable-post-misched=false"]),
     ("kernels_w4.hip", ["-mllvm", "-enable-misched=false", "-mllvm", "-enable-post-misched=false"]),
 ]

@@ -1,0 +1,156 @@
+"""The block kernels (RMSNorm with its residual, SwiGLU, cross-entropy) against
+float64, at the edges of their rows and 16-byte chunks, and next to the torch
+expressions they stand in for.
+
+Tolerances: a bf16 result is within one rounding (2^-8 of the value, with the fp32
+arithmetic's few 2^-22 on top); sums over rows (dg) add sqrt(rows) fp32 roundings of
+the terms; the loss is an fp32 value of fp32 exponentials (2^-20 of the logits'
+range)."""
+import pytest
+
+from gpu_util import BF16_U, LAM, U32, dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+ops = pytest.importorskip("paper_2410_15352_amd._block_ops")
+blk = pytest.importorskip("paper_2410_15352_amd.block")
+
+
+def _rand(*shape, scale=1.0, seed=0):
+    g = torch.Generator(device=dev()).manual_seed(seed + sum(shape))
+    return (scale * torch.randn(*shape, generator=g, device=dev())).to(torch.bfloat16)
+
+
+def _close(a, ref, mag=None, extra=0.0):
+    tol = (BF16_U + 8 * U32) * ref.abs() + extra * (ref.abs() if mag is None else mag) + 1e-30
+    assert a.shape == ref.shape and bool(((a.double() - ref).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("rows,d", [(1, 8), (5, 512), (3, 520), (130, 1024), (4097, 1032), (33, 2736), (17, 4096),
+                                    (9, 4104), (7, 12)])  # the last two take the torch expressions
+@pytest.mark.parametrize("add", [False, True])
+def test_rmsnorm(rows, d, add):
+    norm = blk.RMSNorm(d)
+    with torch.no_grad():
+        norm.weight.copy_(1 + 0.1 * _rand(d))
+    x, o = (_rand(rows, d, seed=s).requires_grad_(True) for s in (1, 2))
+    dh, dr = _rand(rows, d, seed=3), _rand(rows, d, seed=4)
+    assert ops.norm_usable(x, norm.weight) == (d % 8 == 0 and d <= 4096)
+    s, h = norm.add(x, o) if add else norm.with_residual(x)
+    torch.autograd.backward([s, h], [dr, dh])
+    # float64, from the bf16 sum the norm sees
+    xs = (x + o if add else x).detach()
+    assert torch.equal(s, xs)
+    X, g = xs.double(), norm.weight.detach().double()
+    rstd = torch.rsqrt(X.square().mean(-1, keepdim=True) + norm.eps)
+    _close(h, X * rstd * g, extra=8 * U32)
+    gd, xh = dh.double() * g, X * rstd
+    mean = (gd * xh).mean(-1, keepdim=True)
+    dx = rstd * (gd - xh * mean) + dr.double()
+    mag = rstd * (gd.abs() + xh.abs() * (gd * xh).abs().mean(-1, keepdim=True)) + dr.double().abs()
+    # (the torch expressions round the norm's gradient before the residual's is added)
+    _close(x.grad, dx, mag, extra=16 * U32 if ops.norm_usable(x, norm.weight) else BF16_U)
+    assert not add or torch.equal(o.grad, x.grad)
+    t = dh.double() * xh
+    _close(norm.weight.grad, t.sum(0), t.abs().sum(0), extra=LAM * U32 * (8 + rows ** 0.5))
+    y = norm(xs)
+    assert torch.equal(y, h)
+    # deterministic
+    g1 = norm.weight.grad.clone()
+    norm.weight.grad = None
+    s2, h2 = norm.add(x, o) if add else norm.with_residual(x)
+    torch.autograd.backward([s2, h2], [dr, dh])
+    assert torch.equal(g1, norm.weight.grad)
+
+
+def test_rmsnorm_gradient_routes():
+    """x without a gradient, only one of the results used, a recorded backward."""
+    norm, x = blk.RMSNorm(64), _rand(10, 64)
+    _, h = norm.with_residual(x)
+    h.sum().backward()
+    assert norm.weight.grad is not None and x.grad is None
+    x.requires_grad_(True)
+    s, _ = norm.with_residual(x)
+    s.sum().backward()
+    assert torch.equal(x.grad, torch.ones_like(x))
+    y = norm(x)
+    (gx,) = torch.autograd.grad(y.float().square().sum(), x, create_graph=True)
+    gx.float().sum().backward()
+    assert torch.isfinite(x.grad).all()
+
+
+@pytest.mark.parametrize("rows,f", [(1, 8), (3, 24), (257, 1376), (1000, 2736), (5, 12)])  # the last one: torch
+def test_swiglu(rows, f):
+    gu = _rand(rows, 2 * f, scale=2.0).requires_grad_(True)
+    with torch.no_grad():
+        gu[0, :4] = torch.tensor([0.0, 88.0, -100.0, float("inf")])
+    da = _rand(rows, f, seed=9)
+    act = ops.swiglu(gu, f)
+    act.backward(da)
+    g, u, d = gu.detach()[:, :f].double(), gu.detach()[:, f:].double(), da.double()
+    s, sg = (g / (1 + torch.exp(-g))), 1 / (1 + torch.exp(-g))
+    ok = torch.isfinite(g)
+    _close(torch.where(ok, act, 0), torch.where(ok, s * u, 0), extra=2 * BF16_U)
+    _close(torch.where(ok, gu.grad[:, f:], 0), torch.where(ok, d * s, 0), extra=2 * BF16_U)
+    ref, mag = d * u * sg * (1 + g * (1 - sg)), (d * u * sg).abs() * (1 + (g * (1 - sg)).abs())
+    _close(torch.where(ok, gu.grad[:, :f], 0), torch.where(ok, ref, 0), torch.where(ok, mag, 0), extra=2 * BF16_U)
+    if f % 8 == 0:  # bitwise what the separate operations give, infinities and NaN included
+        assert torch.equal(act.view(torch.int16), (torch.nn.functional.silu(gu[:, :f]) * gu[:, f:]).view(torch.int16))
+
+
+@pytest.mark.parametrize("rows,V", [(1, 1), (2, 7), (3, 1003), (64, 1000), (130, 32000), (1025, 2049), (5, 4104)])
+def test_cross_entropy(rows, V):
+    x = _rand(rows, V, scale=3.0).requires_grad_(True)
+    t = torch.randint(V, (rows,), device=dev())
+    if rows > 2:
+        t[1] = ops.IGNORE
+        with torch.no_grad():
+            x[0, 0], x[2, V // 2] = float("-inf"), -3.3895e38  # bf16's lowest value
+        t[0], t[2] = V - 1, 0
+    loss = ops.cross_entropy(x, t)
+    assert loss.dtype == torch.float32 and loss.dim() == 0
+    (2.0 * loss).backward()
+    X = x.detach().double().requires_grad_(True)
+    ref = torch.nn.functional.cross_entropy(X, t)
+    (2.0 * ref).backward()
+    assert abs(loss.item() - ref.item()) <= 2.0 ** -18 * max(1.0, abs(ref.item()))
+    _close(x.grad, X.grad, 2.0 * torch.softmax(X.detach(), -1) / max(rows - 1, 1), extra=2.0 ** -17)
+
+
+def test_cross_entropy_not_finite_and_empty_mean():
+    t = torch.tensor([0, 1, 2], device=dev())
+    for bad in (float("nan"), float("inf")):
+        x = _rand(3, 40)
+        x[1, 5] = bad
+        assert torch.isnan(ops.cross_entropy(x, t)) and torch.isnan(torch.nn.functional.cross_entropy(x.float(), t))
+    x = _rand(3, 40)
+    x[1] = float("-inf")
+    assert torch.isnan(ops.cross_entropy(x, t))
+    x = _rand(3, 40).requires_grad_(True)
+    loss = ops.cross_entropy(x, torch.full_like(t, ops.IGNORE))
+    loss.backward()
+    assert torch.isnan(loss) and torch.equal(x.grad, torch.zeros_like(x))
+    x = _rand(3, 40).requires_grad_(True)
+    (g,) = torch.autograd.grad(ops.cross_entropy(x, t), x, create_graph=True)
+    (g1,) = torch.autograd.grad(ops.cross_entropy(x, t), x)
+    _close(g.detach(), g1.double(), extra=BF16_U)
+    g.float().square().sum().backward()
+    assert torch.isfinite(x.grad).all()
+
+
+@pytest.mark.parametrize("b,l,heads,hd", [(1, 1, 1, 8), (2, 33, 3, 24), (3, 65, 4, 64), (2, 9, 3, 4)])
+def test_split_qkv(b, l, heads, hd):
+    qkv = _rand(b, l, 3, heads, hd).requires_grad_(True)
+    parts = ops.split_qkv(qkv)
+    for i, t in enumerate(parts):
+        assert torch.equal(t, qkv.detach()[:, :, i].transpose(1, 2))
+    dense = [_rand(b, l, heads, hd, seed=i).transpose(1, 2) for i in (1, 2, 3)]  # as attention gives them
+    other = [g.contiguous() for g in dense]                                      # another layout: the same result
+    for grads in (dense, other):
+        qkv.grad = None
+        torch.autograd.backward(ops.split_qkv(qkv), grads)
+        assert torch.equal(qkv.grad, torch.stack([g.transpose(1, 2) for g in dense], 2))
+    qkv.grad = None
+    ops.split_qkv(qkv)[1].backward(dense[1])  # only k is used
+    assert torch.equal(qkv.grad[:, :, 1], dense[1].transpose(1, 2)) and not qkv.grad[:, :, 0::2].any()
