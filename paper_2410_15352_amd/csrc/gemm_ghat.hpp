@@ -28,12 +28,13 @@
 // Pipeline as in gemm_w4.hpp: 32-token K tiles, four LDS stages, copies by
 // buffer_load_dwordx4 ... lds issued 3 K tiles ahead (six stages, 5 ahead, time
 // the same) and spread over the MFMAs, one barrier per K tile:
-//   step 0: read fragments (t, 1); the first half of this wave's copies for
-//           K tile t + 3; the MFMAs on fragments (t, 0)
+//   step 0: the MFMAs on fragments (t, 0); between them the reads of fragments
+//           (t, 1), one fragment per MFMA, and the first half of this wave's
+//           copies for K tile t + 3
 //   step 1: wait for this wave's copies of K tile t + 1 (the copies of K tile
 //           t + 2 and the first half of t + 3 may still be in flight);
-//           barrier; read fragments (t + 1, 0); the second half of the
-//           copies; the MFMAs on fragments (t, 1)
+//           barrier; the MFMAs on fragments (t, 1); between them the reads of
+//           fragments (t + 1, 0) and the second half of the copies
 //
 // LDS (bytes from the dynamic base): stage s of z^T at s * TM * 64 ([32][TM]
 // bf16), stage s of dL/do at 4 * TM * 64 + s * TN * 64 ([32][TN] bf16).
@@ -189,23 +190,21 @@ __device__ __forceinline__ u32x4 gh_frag(uint32_t stage, int n0, int kk, int lan
   return out;
 }
 
-// Fragments of 16-deep step kk of the stage at LDS byte offsets (sa, sb):
-// rows r0 .. r0 + 32 FM - 1 of z^T, columns c0 .. c0 + 127 of dL/do.
+// Fragment f (rows first, then columns) of 16-deep step kk of the stage at LDS byte
+// offsets (sa, sb): rows r0 .. r0 + 32 FM - 1 of z^T, columns c0 .. c0 + 127 of dL/do.
 template <int SHAPE>
-__device__ __forceinline__ void gh_read(uint32_t lbase, uint32_t sa, uint32_t sb, int r0, int c0, int lane, int kk,
+__device__ __forceinline__ void gh_read(uint32_t lbase, uint32_t sa, uint32_t sb, int r0, int c0, int lane, int kk, int f,
                                         u32x4 (&fa)[GhShape<SHAPE>::kFm], u32x4 (&fb)[4]) {
   using S = GhShape<SHAPE>;
-#pragma unroll
-  for (int i = 0; i < S::kFm; ++i) fa[i] = gh_frag<S::kTm>(lbase + sa, r0 + i * 32, kk, lane);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) fb[j] = gh_frag<S::kTn>(lbase + sb, c0 + j * 32, kk, lane);
+  if (f < S::kFm) fa[f] = gh_frag<S::kTm>(lbase + sa, r0 + f * 32, kk, lane);
+  else fb[f - S::kFm] = gh_frag<S::kTn>(lbase + sb, c0 + (f - S::kFm) * 32, kk, lane);
 }
 
 // The G^ partial tile of workgroup (split, layer, column tile, row tile).
 template <int SHAPE>
 __device__ __forceinline__ void ghat_w4(const GhatW4Params& prm) {
   using S = GhShape<SHAPE>;
-  constexpr int FM = S::kFm, NM = S::kFm * S::kFn;  // fragments (rows), MFMAs per step
+  constexpr int FM = S::kFm, NM = S::kFm * S::kFn, NF = FM + 4;  // row fragments; MFMAs and fragments per step
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // this wave's rows and columns inside the tile: 2 x 2 waves for the
@@ -244,10 +243,13 @@ __device__ __forceinline__ void ghat_w4(const GhatW4Params& prm) {
   // copy c (0 .. kCopies - 1) of this wave for K tile u into stage u % 4;
   // tokens past this split's K tiles or past T land out of range (the last
   // split is the only one whose K tiles run past T)
+  // (the strides are local copies: read through p they are loaded again every K
+  // tile, and the wait for that load also waits for every LDS read in flight)
+  const uint32_t kstep_z = static_cast<uint32_t>(kGhK * p.ldz * 2), kstep_y = static_cast<uint32_t>(kGhK * p.lddy * 2);
   auto copy = [&](int u, int c) {
     const int st = u % kGhStages;
-    const uint32_t krow_bytes_z = static_cast<uint32_t>(u) * kGhK * p.ldz * 2;
-    const uint32_t krow_bytes_y = static_cast<uint32_t>(u) * kGhK * p.lddy * 2;
+    const uint32_t krow_bytes_z = static_cast<uint32_t>(u) * kstep_z;
+    const uint32_t krow_bytes_y = static_cast<uint32_t>(u) * kstep_y;
     const uint32_t oob = u < kt ? 0u : kW4Oob;
     if (c < S::kACopies) {
       const uint32_t dst = lbase + st * S::kAStage + static_cast<uint32_t>(wave * S::kACopies + c) * 1024u;
@@ -277,18 +279,19 @@ __device__ __forceinline__ void ghat_w4(const GhatW4Params& prm) {
       for (int c = 0; c < S::kCopies; ++c) copy(u, c);
     w4_wait_vm<0>();
     asm volatile("s_barrier" ::: "memory");
-    gh_read<SHAPE>(lbase, 0, S::kBBase, wr0, wc0, lane, 0, fa[0], fb[0]);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) gh_read<SHAPE>(lbase, 0, S::kBBase, wr0, wc0, lane, 0, f, fa[0], fb[0]);
     gh_wait_frags<FM>(fa, fb);
     for (int t = 0; t < kt; ++t) {
       const uint32_t st0 = static_cast<uint32_t>(t % kGhStages), st1 = static_cast<uint32_t>((t + 1) % kGhStages);
       const uint32_t sa = st0 * S::kAStage, sb = S::kBBase + st0 * S::kBStage;
       const uint32_t sa1 = st1 * S::kAStage, sb1 = S::kBBase + st1 * S::kBStage;
       // step 0
-      gh_read<SHAPE>(lbase, sa, sb, wr0, wc0, lane, 1, fa[1], fb[1]);
 #pragma unroll
       for (int i = 0; i < NM; ++i) {
         const int fi = i >> 2, fj = i & 3;
         acc[fi][fj] = mfma32x32x16(fa[0][fi], fb[0][fj], acc[fi][fj]);
+        if (i < NF) gh_read<SHAPE>(lbase, sa, sb, wr0, wc0, lane, 1, i, fa[1], fb[1]);
         if (i % S::kEvery == 0) copy(t + kGhAhead, i / S::kEvery);
       }
       gh_pin_acc<FM>(acc);
@@ -296,11 +299,11 @@ __device__ __forceinline__ void ghat_w4(const GhatW4Params& prm) {
       // copies of the next kGhAhead - 2 K tiles and the step-0 copies of the
       // one after are in flight
       gh_wait_barrier<S::kCopies * (kGhAhead - 2) + kStep0, FM>(fa, fb);
-      gh_read<SHAPE>(lbase, sa1, sb1, wr0, wc0, lane, 0, fa[0], fb[0]);
 #pragma unroll
       for (int i = 0; i < NM; ++i) {
         const int fi = i >> 2, fj = i & 3;
         acc[fi][fj] = mfma32x32x16(fa[1][fi], fb[1][fj], acc[fi][fj]);
+        if (i < NF) gh_read<SHAPE>(lbase, sa1, sb1, wr0, wc0, lane, 0, i, fa[0], fb[0]);
         if (i % S::kEvery == 0) copy(t + kGhAhead, kStep0 + i / S::kEvery);
       }
       gh_wait_frags<FM>(fa, fb);
@@ -311,7 +314,128 @@ __device__ __forceinline__ void ghat_w4(const GhatW4Params& prm) {
   const int64_t ldp = static_cast<int64_t>(p.tiles_m) * S::kTn;
   float* out = p.part + static_cast<int64_t>(split) * (p.tiles_r * S::kTm) * ldp;
   const int64_t r0 = row0 + wr0, c0 = col0 + wc0;
+  // (the padding rows too: leaving them out by a test per store took the kernel from
+  // 66 to 85 us at r = 342)
   for_each_acc(acc, lane, [&](int row, int col, float v) { out[(r0 + row) * ldp + c0 + col] = v; });
+}
+
+// G^ of few tokens in one launch, without partial sums in memory: one workgroup per
+// 64 x 64 tile, its four waves taking every fourth 32-token K tile with LDS stages
+// of their own (3 x 8 KB each, no barrier in the loop), their sums added in wave
+// order through LDS.  The split-K kernel and its reduction cost at least 14 us
+// (33 MB of partial sums written and read whatever the token count); here the time
+// is the copies of a CU, (64 + 64) columns of every token at about 55 KB per us:
+// 4.65 us per 1000 tokens.  gate|up of LLaMA-60M, 1000 tokens: 16 -> 7 us.
+//
+// LDS rows are 128 bytes here, chunk c of K row k at c ^ (4 ((k >> 1) & 1)): the 4
+// K rows x 64 bytes of a transposing read fill the 64 banks.
+constexpr int kGdTile = 64, kGdStages = 3;
+constexpr uint32_t kGdOperand = kGhK * kGdTile * 2, kGdStage = 2 * kGdOperand;  // 4 KB, 8 KB
+constexpr size_t kGdLds = size_t(4) * kGdStages * kGdStage;                     // 96 KB
+
+struct GhatDirectParams {
+  GhatW4Layer layer[kGhMaxLayers];   // part unused; tiles of 64 x 64
+  float* G[kGhMaxLayers];            // [r][m]
+  int tile_begin[kGhMaxLayers + 1];
+  int count, T, accumulate;
+};
+
+__device__ __forceinline__ u32x4 gd_frag(uint32_t stage, int n0, int kk, int lane) {
+  const int g = lane >> 4, s = lane & 15;
+  const int j = s >> 2, q = s & 3;
+  const int col = n0 + (g & 1) * 16 + q * 4;
+  u32x4 out;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int k = kk * 16 + (g >> 1) * 8 + 4 * h + j;
+    const int chunk = (col >> 3) ^ (4 * ((k >> 1) & 1));
+    const u32x2 v = gh_tr_read(stage + 2u * static_cast<uint32_t>(k * kGdTile + chunk * 8 + (col & 7)));
+    out[2 * h] = v.x;
+    out[2 * h + 1] = v.y;
+  }
+  return out;
+}
+
+__device__ __forceinline__ void ghat_direct(const GhatDirectParams& prm) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tile_all = static_cast<int>(xcd_remap(blockIdx.x, gridDim.x));
+  const int li = batch_layer_of(prm.tile_begin, prm.count, tile_all);
+  const GhatW4Layer& p = prm.layer[li];
+  const int tile = tile_all - prm.tile_begin[li];
+  const int ct = tile / p.tiles_r, rt = tile % p.tiles_r;
+  const int row0 = rt * kGdTile, col0 = ct * kGdTile;
+  const int kt = (prm.T + kGhK - 1) / kGhK;
+  const __amdgpu_buffer_rsrc_t rz = w4_rsrc(p.z + row0, view_bytes(prm.T, p.r, p.ldz, 0, row0, 2));
+  const __amdgpu_buffer_rsrc_t ry = w4_rsrc(p.dy + col0, view_bytes(prm.T, p.m, p.lddy, 0, col0, 2));
+  // copy block q: K rows 8 q .. + 7, 128 bytes each; lane L lands at K row 8 q + L / 8,
+  // physical chunk L % 8
+  const int krow = lane >> 3, chunk = (lane & 7) ^ (4 * ((krow >> 1) & 1));
+  const uint32_t voz = static_cast<uint32_t>(krow * p.ldz * 2 + 16 * chunk);
+  const uint32_t voy = static_cast<uint32_t>(krow * p.lddy * 2 + 16 * chunk);
+  const uint32_t qz = static_cast<uint32_t>(16 * p.ldz), qy = static_cast<uint32_t>(16 * p.lddy);  // 8 K rows
+  const uint32_t lbase = __builtin_amdgcn_groupstaticsize() + static_cast<uint32_t>(wave) * (kGdStages * kGdStage);
+  auto copy = [&](int u, int st, int c) {  // c = 0 .. 7: z^T blocks, then dL/do blocks
+    const uint32_t oob = u < kt ? 0u : kW4Oob;
+    const uint32_t dst = lbase + static_cast<uint32_t>(st) * kGdStage + static_cast<uint32_t>(c) * 1024u;
+    const uint32_t vo = c < 4 ? voz + (4u * u + c) * qz : voy + (4u * u + (c - 4)) * qy;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(c < 4 ? rz : ry, reinterpret_cast<w4_lds_void*>(static_cast<uintptr_t>(dst)),
+                                             16, static_cast<int>(vo | oob), 0, 0, 0);
+  };
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kGdStages - 1; ++s)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) copy(wave + 4 * s, s, c);
+  int st = 0;
+  for (int u = wave; u < kt; u += 4) {
+    // this wave's copies of K tile u have landed; its reads of the stage that is
+    // filled next returned before the last MFMAs
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * (kGdStages - 2)) : "memory");
+    const uint32_t sa = lbase + static_cast<uint32_t>(st) * kGdStage, sb = sa + kGdOperand;
+    const int nst = st == 0 ? kGdStages - 1 : st - 1;
+    u32x4 fa[2][2], fb[2][2];  // [kk][fragment]
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        fa[kk][f] = gd_frag(sa, 32 * f, kk, lane);
+        fb[kk][f] = gd_frag(sb, 32 * f, kk, lane);
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(fa[0][0]), "+v"(fa[0][1]), "+v"(fa[1][0]), "+v"(fa[1][1]), "+v"(fb[0][0]), "+v"(fb[0][1]),
+                   "+v"(fb[1][0]), "+v"(fb[1][1])
+                 :
+                 : "memory");
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int kk = m >> 2, i = (m >> 1) & 1, j = m & 1;
+      acc[i][j] = mfma32x32x16(fa[kk][i], fb[kk][j], acc[i][j]);
+      copy(u + 4 * (kGdStages - 1), nst, m);
+    }
+    st = st == kGdStages - 1 ? 0 : st + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy may still be writing LDS
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  float* part = reinterpret_cast<float*>(lds);  // [wave][64][64]
+  __syncthreads();
+  for_each_acc(acc, lane, [&](int row, int col, float v) { part[wave * 4096 + row * 64 + col] = v; });
+  __syncthreads();
+  float* G = prm.G[li];
+#pragma unroll 4
+  for (int i = 0; i < 16; ++i) {
+    const int row = (tid >> 6) + 4 * i, e = row * 64 + lane;
+    if (row0 + row >= p.r || col0 + lane >= p.m) continue;
+    const float v = ((part[e] + part[4096 + e]) + part[8192 + e]) + part[12288 + e];
+    float* o = G + static_cast<int64_t>(row0 + row) * p.m + col0 + lane;
+    *o = prm.accumulate ? *o + v : v;
+  }
 }
 
 }  // namespace compact

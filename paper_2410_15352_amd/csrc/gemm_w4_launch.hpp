@@ -26,6 +26,9 @@ hipError_t gemm_w4_launch(const W4Gemm& g, W4Use use, hipStream_t stream);
 // G^ partials: one workgroup per (split, layer, column tile, row tile).
 hipError_t ghat_w4_launch(const GhatW4Params& p, hipStream_t stream);
 
+// G^ of few tokens without partial sums: one workgroup per 64 x 64 tile.
+hipError_t ghat_direct_launch(const GhatDirectParams& p, hipStream_t stream);
+
 // True when the decompression kernel takes a layer of this shape and layout.
 bool dec_w4_eligible(int64_t n, int64_t m, int64_t r, int64_t ldw, int64_t ldn, int64_t ldpt, bool w_f32);
 

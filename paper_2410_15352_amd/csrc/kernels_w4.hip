@@ -23,6 +23,8 @@ __global__ __launch_bounds__(256, 1) void k_ghat_w4(GhatW4Params p) {
   ghat_w4<SHAPE>(p);
 }
 
+__global__ __launch_bounds__(256, 1) void k_ghat_direct(GhatDirectParams p) { ghat_direct(p); }
+
 // Four workgroups per CU for bf16 W (at most 128 registers per lane), two for fp32 W.
 template <bool WF32>
 __global__ __launch_bounds__(256, WF32 ? 2 : 4) void k_dec_w4(DecW4Batch d) {
@@ -36,7 +38,7 @@ namespace {
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_cus[kMaxDevices];        // CU count per device, 0 until queried
 constexpr int kGemmVariants = 16;
-std::atomic<bool> g_lds_set[kMaxDevices][kGemmVariants + 3];  // dynamic LDS limit raised: k_gemm_w4, k_ghat_w4
+std::atomic<bool> g_lds_set[kMaxDevices][kGemmVariants + 4];  // dynamic LDS limit raised: k_gemm_w4, k_ghat_w4, k_ghat_direct
 
 bool fits_offsets(int64_t ld, int64_t K) {
   // 32-bit buffer offsets: 256 rows of ld elements plus K, in bytes
@@ -161,6 +163,23 @@ hipError_t ghat_w4_launch(const GhatW4Params& p, hipStream_t stream) {
     hipLaunchKernelGGL(k_ghat_w4<2>, grid, dim3(256), lds[2], stream, p);
   else
     hipLaunchKernelGGL(k_ghat_w4<0>, grid, dim3(256), lds[0], stream, p);
+  return hipGetLastError();
+}
+
+hipError_t ghat_direct_launch(const GhatDirectParams& p, hipStream_t stream) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  if (!g_lds_set[dev][kGemmVariants + 3].load(std::memory_order_acquire)) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_ghat_direct), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(kGdLds));
+    if (e != hipSuccess) return e;
+    g_lds_set[dev][kGemmVariants + 3].store(true, std::memory_order_release);
+  }
+  const int blocks = p.tile_begin[p.count];
+  if (blocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_ghat_direct, dim3(static_cast<uint32_t>(blocks)), dim3(256), kGdLds, stream, p);
   return hipGetLastError();
 }
 

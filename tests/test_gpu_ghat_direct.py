@@ -1,0 +1,46 @@
+"""G^ of few tokens (one launch, 64 x 64 tiles, the waves splitting the tokens)
+against float64, at the edges of its tiles and 32-token K tiles, for groups and in
+accumulate mode; operands are column slices whose padding and neighbours hold NaN.
+The bound is an fp32 sum over the tokens of exact products (acc_bound)."""
+import numpy as np
+import pytest
+
+from gpu_util import U32, acc_bound, dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+cp = pytest.importorskip("paper_2410_15352_amd")
+
+
+def _slice(rows, cols, seed, scale):
+    g = torch.Generator(device=dev()).manual_seed(seed)
+    buf = torch.full((rows, (cols + 7) // 8 * 8 + 16), float("nan"), dtype=torch.bfloat16, device=dev())
+    v = buf[:, 8:8 + cols]
+    v.copy_((scale * torch.randn(rows, cols, generator=g, device=dev())).to(torch.bfloat16))
+    return v
+
+
+@pytest.mark.parametrize("T,ms,rs", [
+    (1, [8], [8]), (31, [64], [64]), (33, [65], [63]), (127, [1], [1]), (129, [200, 33], [72, 65]),
+    (1000, [1376, 1376], [128, 128]), (1025, [520] * 7 + [513], [40] * 8), (2047, [1030], [342]),
+    (300, [5461], [512]),
+])
+def test_ghat_direct(T, ms, rs):
+    n = max(64, *rs)
+    dy, z = _slice(T, sum(ms), T, 0.01), _slice(T, sum(rs), T + 1, 2.0)
+    ws = torch.empty(cp.bwd_group_workspace_bytes(T, n, ms, rs), dtype=torch.uint8, device=dev())
+    G = [torch.empty(r, m, device=dev()) for r, m in zip(rs, ms)]
+    cp.compact_bwd_group(dy, None, z, None, G, ms, rs, ws=ws)
+    G2 = [torch.randn(r, m, device=dev()) for r, m in zip(rs, ms)]
+    ref2 = [a + b for a, b in zip(G2, G)]
+    cp.compact_bwd_group(dy, None, z, None, G2, ms, rs, ws=ws, accumulate=True)
+    for a, b in zip(G2, ref2):
+        assert torch.equal(a, b)
+    D, Z, mo, ro = to_np(dy), to_np(z), 0, 0
+    for g, m, r in zip(G, ms, rs):
+        zt, d = Z[:, ro:ro + r].T, D[:, mo:mo + m]
+        ref = zt @ d
+        err = np.abs(g.cpu().numpy().astype(np.float64) - ref)
+        assert (err <= acc_bound(T) * (np.abs(zt) @ np.abs(d)) + U32 * np.abs(ref)).all()
+        mo, ro = mo + m, ro + r
