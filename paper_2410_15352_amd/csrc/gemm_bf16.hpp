@@ -254,9 +254,10 @@ __device__ __forceinline__ void for_each_acc(const f32x16 (&acc)[FM][FN], int la
 // ---------------------------------------------------------------------------
 template <int WTM, int WTN>
 __device__ __forceinline__ int stage_dword(int row, int dw) {
-  static_assert(WTN % 128 == 0 || WTN == 64, "staging swizzle assumes 64 or 128k columns");
+  static_assert(WTN % 128 == 0 || WTN == 64 || WTN == 32, "staging swizzle assumes 32, 64 or 128k columns");
   constexpr int kRowDw = WTN / 2;
-  const int sw = WTN >= 128 ? (((row >> 1) & 3) << 4) : (((row >> 1) & 1) << 4);
+  // (32 columns: the two rows of a half wave are 32 dwords apart as they are)
+  const int sw = WTN >= 128 ? (((row >> 1) & 3) << 4) : WTN == 64 ? (((row >> 1) & 1) << 4) : 0;
   return row * kRowDw + (dw ^ sw);
 }
 

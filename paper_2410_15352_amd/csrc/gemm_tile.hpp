@@ -19,14 +19,14 @@
 // waves share it (a 128 x 128 tile alone on the chip: 0.57 us per step with
 // bursts).
 //
-// What bounds it: with few tiles, the K step of one workgroup (128 x 256: 0.57 us
-// per 64-deep step alone on the chip, 128 x 128: 0.37, 64 x 64: 0.25; the MFMAs
+// What bounds it: with few tiles, the K step of one workgroup (256 x 128: 0.57 us
+// per 64-deep step alone on the chip, 128 x 128: 0.35, 64 x 64: 0.235; the MFMAs
 // alone 0.43, 0.21, 0.05); with every CU busy, the operand bytes through L2
 // (about 13 TB/s over the chip).  The persistent kernel moves fewer bytes per
 // flop, so it stays the better one when its tiles fill the CUs; below that
-// (M x N, K; persistent -> tile kernel, MI355X): 8192 x 1024, 3072: 70 -> 49 us;
-// 8192 x 512, 2752: 55 -> 27 us; 4096 x 1024, 3072: 62 -> 30 us; 1000 x 512,
-// 2752: 52 -> 15 us; 1024 x 1920, 512: 18.3 -> 6.5 us.
+// (M x N, K; persistent -> tile kernel, MI355X): 8192 x 1024, 3072: 71 -> 50 us;
+// 8192 x 512, 2752: 55 -> 26.5 us; 4096 x 1024, 3072: 62 -> 29 us; 1000 x 512,
+// 2752: 52 -> 13.1 us; 1024 x 1920, 512: 18.3 -> 6.2 us.
 //
 // LDS: stage s holds A [BM][64] and B [BN][64] at s * (BM + BN) * 128 bytes.
 // Logical 16-byte chunk c of row R sits at c ^ ((R >> 1) & 7): the 16 rows that
@@ -222,7 +222,7 @@ __device__ __forceinline__ void gemm_tile(const TGemm& g) {
 
 // The tile shapes that are built (kernels_tile.hip), and the persistent
 // 256 x 256 kernel as the fifth choice.
-enum class TileKind : int { k128x256 = 0, k128x128 = 1, k64x128 = 2, k64x64 = 3, kPersistent = 4 };
+enum class TileKind : int { k256x128 = 0, k128x128 = 1, k64x128 = 2, k64x64 = 3, kPersistent = 4 };
 constexpr int kTileKinds = 4;
 
 // The kernel that should compute an M x (n0 + n1) product over K (n1 = 0: one

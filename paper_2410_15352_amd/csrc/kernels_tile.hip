@@ -33,11 +33,13 @@ Variant variant() {
                  BM, BN, T::kThreads, T::kLds};
 }
 
-// Eight waves for the two large tiles (two per SIMD), four and two for the small
-// ones; LDS for one, one, two and three workgroups per CU.
+// Eight waves (two per SIMD) for all but the smallest tile, which has four: what
+// bounds a small tile is the issue of its copies, reads and MFMAs, and more waves
+// issue more (64 x 64 with two waves: 15.1 us for 1000 x 512 over K 2752, with four
+// 13.1).  LDS for one, one, two and three workgroups per CU.
 const Variant& variant_of(int kind) {
-  static const Variant v[kTileKinds] = {variant<128, 256, 2, 4, 3>(), variant<128, 128, 4, 2, 4>(),
-                                        variant<64, 128, 2, 2, 3>(), variant<64, 64, 2, 1, 3>()};
+  static const Variant v[kTileKinds] = {variant<256, 128, 4, 2, 3>(), variant<128, 128, 2, 4, 4>(),
+                                        variant<64, 128, 2, 4, 3>(), variant<64, 64, 2, 2, 3>()};
   return v[kind];
 }
 
@@ -45,21 +47,26 @@ const Variant& variant_of(int kind) {
 // (256 to 32768 rows, 512 to 5728 columns, K 512 to 5472): the tiles run in
 // rounds of `slots` per CU; a 64-deep K step of a round takes `alone` with few
 // workgroups on the chip and `full` with all slots taken (the copies then share
-// L2), a round `ov` more (first copies and output), the launch `base`.
+// L2), a round `ov` more (first copies and output), the launch `base`.  Over many
+// rounds, or with several workgroups per CU, a CU takes the next tile when it is
+// free and a part of a round costs its part; otherwise the last round lasts as long
+// as a tile.  The persistent kernel deals its tiles out beforehand (always the
+// latter).
 struct TileCost {
   int rows, cols, slots;
   double alone, full, ov, base;
 };
 constexpr TileCost kCost[kTileKinds + 1] = {
-    {128, 256, 1, 0.57, 0.92, 5.0, 3.0}, {128, 128, 1, 0.37, 0.55, 3.0, 3.0}, {64, 128, 2, 0.28, 0.62, 3.0, 3.0},
-    {64, 64, 3, 0.25, 0.68, 3.0, 3.0},   {256, 256, 1, 1.08, 1.62, 3.5, 5.0},
+    {256, 128, 1, 0.57, 0.863, 5.6, 3.0}, {128, 128, 1, 0.35, 0.485, 3.2, 3.0}, {64, 128, 2, 0.21, 0.62, 2.0, 3.0},
+    {64, 64, 3, 0.14, 0.61, 1.2, 3.0},    {256, 256, 1, 1.08, 1.65, 4.0, 5.5},
 };
 
-double tile_cost(const TileCost& c, int64_t M, int64_t n0, int64_t n1, int64_t K, int cus) {
+double tile_cost(int k, int64_t M, int64_t n0, int64_t n1, int64_t K, int cus) {
+  const TileCost& c = kCost[k];
   const double tiles = double(ceil_div(M, c.rows)) * double(ceil_div(n0, c.cols) + ceil_div(n1, c.cols));
-  const double steps = double(ceil_div(K, 64));
-  const double per = double(cus) * c.slots;
-  const double full = double(int64_t(tiles / per)), rest = tiles - full * per;
+  const double steps = double(ceil_div(K, 64)), per = double(cus) * c.slots, rounds = tiles / per;
+  if (k < kTileKinds && rounds > (c.slots > 1 ? 1.0 : 4.0)) return c.base + rounds * (c.ov + steps * c.full);
+  const double full = double(int64_t(rounds)), rest = tiles - full * per;
   const double part = rest > 0 ? c.ov + steps * (c.alone + (c.full - c.alone) * rest / per) : 0.0;
   return c.base + full * (c.ov + steps * c.full) + part;
 }
@@ -82,13 +89,13 @@ hipError_t device_cus(int* cus) {
   return hipSuccess;
 }
 
-// The cheapest kernel by the measured costs; a tile kernel has to win by 8%,
-// about the error of the estimate.
+// The cheapest kernel by the measured costs; a tile kernel has to win by 5%, about
+// the error of the estimate.
 TileKind gemm_tile_choose(int64_t M, int64_t n0, int64_t n1, int64_t K, bool persistent, int cus) {
   int best = kTileKinds;
-  double t = persistent ? 0.92 * tile_cost(kCost[kTileKinds], M, n0, n1, K, cus) : HUGE_VAL;
+  double t = persistent ? 0.95 * tile_cost(kTileKinds, M, n0, n1, K, cus) : HUGE_VAL;
   for (int k = 0; k < kTileKinds; ++k) {
-    const double c = tile_cost(kCost[k], M, n0, n1, K, cus);
+    const double c = tile_cost(k, M, n0, n1, K, cus);
     if (c < t) {
       t = c;
       best = k;

@@ -1,4 +1,4 @@
-"""The tile GEMMs (one workgroup per 128 x 256, 128 x 128, 64 x 128 or 64 x 64
+"""The tile GEMMs (one workgroup per 256 x 128, 128 x 128, 64 x 128 or 64 x 64
 output tile), which take the bf16 forward and dL/dx where the persistent kernel
 would leave CUs without a tile.  Row t of y, z and dL/dx depends on row t of the
 input alone and every bf16 GEMM sums K in the same order, so the first T rows
@@ -35,7 +35,7 @@ CASES = [
     (257, 392, 1376, 64), (1000, 512, 1381, 128),                      # 64 x 64, 64 x 128
     (1025, 509, 1536, 384), (2047, 2736, 1023, 342),                   # 64 x 128
     (4097, 1021, 1000, 128), (3333, 1461, 701, 200),                   # 128 x 128
-    (8191, 3072, 1030, 250), (8192, 1024, 3075, 128),                  # 128 x 256
+    (8191, 3072, 1030, 250), (8192, 1024, 3075, 128),                  # 256 x 128
     (200, 40, 24, 8), (129, 265, 129, 65), (77, 8, 5472, 4),           # K below the persistent kernel's least
 ]
 LONG = 36864
