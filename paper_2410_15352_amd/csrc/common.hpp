@@ -64,4 +64,19 @@ __device__ __forceinline__ int batch_layer_of(const int* begin, int count, int b
 __host__ __device__ constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 __host__ __device__ constexpr int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
+// Layer tables of Alg. 3's launches: sizes once per distinct shape.
+constexpr int kStepShapes = 8;  // distinct shapes per launch
+
+struct StepShape {
+  int n, m, r, ldw;
+};
+
+// Scratch of a layer: N [r][round_up(m, 8)], then (bf16) P^T [r][round_up(n, 64)],
+// each on a 256-byte boundary.
+__host__ __device__ inline int64_t step_ldn(int64_t m) { return round_up(m, 8); }
+__host__ __device__ inline int64_t step_ldpt(int64_t n) { return round_up(n, 64); }
+__host__ __device__ inline int64_t step_n_bytes(int64_t m, int64_t r, int esz) {
+  return round_up(r * step_ldn(m) * esz, int64_t(256));
+}
+
 }  // namespace compact

@@ -1043,10 +1043,14 @@ namespace {
 
 // Per-layer launch description of Alg. 3 (Adam + P^T staging, decompression).
 struct StepPlan {
-  AdamLayer al;
-  int adam_blocks, pt_blocks;
-  DecW4Layer dl;
-  int dec_tiles;
+  StepShape shape;
+  const float* G;
+  float *M, *V;
+  void* W;
+  PhiloxKey key;
+  size_t offset;  // of the layer's scratch in the workspace, a multiple of 256
+  float coef;
+  int64_t adam_blocks, pt_blocks, dec_tiles;
 };
 
 int validate_step(const void* W, int64_t ldw, const float* G, const float* M, const float* V, int64_t n,
@@ -1087,76 +1091,91 @@ AdamConsts adam_consts(int64_t t, double beta1, double beta2, double eps, int pr
   return c;
 }
 
-// `ws` is this layer's scratch (step_layer_bytes, 256-byte aligned).
+// `offset`: this layer's scratch (step_layer_bytes) in the workspace.
 void plan_step(void* W, int64_t ldw, const float* G, float* M, float* V, int64_t n, int64_t m, int64_t r,
-               uint64_t seed, double lr, double alpha, int proj, int dtype, void* ws, StepPlan& P) {
-  const int64_t ldn = n_ld(m), ldpt = pt_ld(n);
-  char* base = static_cast<char*>(ws);
-  AdamLayer& a = P.al;
-  a = AdamLayer{};
-  a.G = G; a.M = M; a.V = V; a.N = base;
-  a.ldn = static_cast<int>(ldn);
-  a.r = static_cast<int>(r);
-  a.m = static_cast<int>(m);
-  a.n = static_cast<int>(n);
-  a.key = philox_key(seed);
+               uint64_t seed, double lr, double alpha, int proj, int dtype, size_t offset, StepPlan& P) {
+  P = StepPlan{};
+  P.shape = StepShape{static_cast<int>(n), static_cast<int>(m), static_cast<int>(r), static_cast<int>(ldw)};
+  P.G = G; P.M = M; P.V = V; P.W = W;
+  P.key = philox_key(seed);
+  P.offset = offset;
+  P.coef = static_cast<float>(lr * alpha * proj_scale64(proj, r));
   P.adam_blocks = adam_blocks(r, m);
-  P.pt_blocks = 0;
-  P.dec_tiles = 0;
-  const double coef64 = lr * alpha * proj_scale64(proj, r);
-  DecW4Layer& d = P.dl;
-  d = DecW4Layer{};
-  d.coef = static_cast<float>(coef64);
   if (dtype != COMPACT_BF16) return;
-  uint16_t* pt = reinterpret_cast<uint16_t*>(
-      base + round_up(static_cast<int64_t>(size_t(r) * size_t(ldn) * elem_size(dtype)), kWsAlign));
-  a.pt = pt;
-  a.ldpt = static_cast<int>(ldpt);
-  P.pt_blocks = pt_blocks(proj_desc(proj, r).kind, r, ldpt);
-  d.W = W; d.ldw = static_cast<int>(ldw);
-  d.N = static_cast<const uint16_t*>(a.N); d.ldn = static_cast<int>(ldn);
-  d.pt = pt; d.ldpt = static_cast<int>(ldpt);
-  d.n = static_cast<int>(n); d.m = static_cast<int>(m); d.r = static_cast<int>(r);
-  d.tiles_c = static_cast<int>(ceil_div(m, kDecT));
-  P.dec_tiles = static_cast<int>(ceil_div(n, kDecT) * d.tiles_c);
+  P.pt_blocks = pt_blocks(proj_desc(proj, r).kind, r, pt_ld(n));
+  P.dec_tiles = ceil_div(n, kDecT) * ceil_div(m, kDecT);
 }
 
-// Adam (+ P^T staging) for every layer of `plans`, then the decompression, in
-// equal groups of at most kStepBatch layers per launch.
-int launch_step_groups(const std::vector<StepPlan>& plans, const AdamConsts& c, int dtype, int w_dtype,
-                       hipStream_t s) {
+// The layers of one launch's table: as many of plans[i0 ..] as hold at most
+// `max_layers` layers, kStepShapes distinct shapes and 2^30 workgroups.  Fills
+// the table's shapes and each layer's shape index.
+int64_t take_layers(const std::vector<StepPlan>& plans, int64_t i0, int64_t max_layers, bool adam,
+                    StepShape* shape, uint8_t* shape_of) {
+  int shapes = 0;
+  int64_t k = 0, blocks = 0;
+  const int64_t left = static_cast<int64_t>(plans.size()) - i0;
+  for (; k < left && k < max_layers; ++k) {
+    const StepPlan& P = plans[i0 + k];
+    blocks += adam ? P.adam_blocks + P.pt_blocks : P.dec_tiles;
+    if (k > 0 && blocks > int64_t(1) << 30) break;
+    int f = 0;
+    while (f < shapes && (shape[f].n != P.shape.n || shape[f].m != P.shape.m || shape[f].r != P.shape.r ||
+                          shape[f].ldw != P.shape.ldw))
+      ++f;
+    if (f == shapes) {
+      if (shapes == kStepShapes) break;
+      shape[shapes++] = P.shape;
+    }
+    shape_of[k] = static_cast<uint8_t>(f);
+  }
+  return k;
+}
+
+// Layers per launch so that `count` layers make equal launches of at most `most`.
+int64_t even_share(int64_t count, int64_t most) { return ceil_div(count, ceil_div(count, most)); }
+
+// Adam (+ P^T staging) for every layer of `plans`, then the decompression, in as
+// few launches as the layer tables allow.
+int launch_steps(const std::vector<StepPlan>& plans, const AdamConsts& c, int dtype, int w_dtype, void* ws,
+                 hipStream_t s) {
   int st;
-  const int count = static_cast<int>(plans.size());
-  const int groups = (count + kStepBatch - 1) / kStepBatch;
-  const int per = (count + groups - 1) / groups;
-  for (int i0 = 0; i0 < count; i0 += per) {
+  const int64_t count = static_cast<int64_t>(plans.size());
+  for (int64_t i0 = 0; i0 < count;) {
     StepBatch b{};
     b.c = c;
-    b.count = std::min(per, count - i0);
-    b.adam_begin[0] = 0;
-    b.pt_begin[0] = 0;
-    for (int j = 0; j < b.count; ++j) {
+    b.ws = static_cast<char*>(ws);
+    const int64_t k = take_layers(plans, i0, even_share(count, kStepBatch), true, b.shape, b.shape_of);
+    b.count = static_cast<int>(k);
+    int64_t ab = 0, pb = 0;
+    for (int64_t j = 0; j < k; ++j) {
       const StepPlan& P = plans[i0 + j];
-      b.layer[j] = P.al;
-      b.adam_begin[j + 1] = b.adam_begin[j] + P.adam_blocks;
-      b.pt_begin[j + 1] = b.pt_begin[j] + P.pt_blocks;
+      b.G[j] = P.G; b.M[j] = P.M; b.V[j] = P.V; b.key[j] = P.key;
+      b.base[j] = static_cast<uint32_t>(P.offset / kWsAlign);
+      ab += P.adam_blocks;
+      pb += P.pt_blocks;
+      b.adam_begin[j + 1] = static_cast<int>(ab);
+      b.pt_begin[j + 1] = static_cast<int>(pb);
     }
-    const int blocks = b.adam_begin[b.count] + b.pt_begin[b.count];
-    hipLaunchKernelGGL(k_adam_pt_batched, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, b);
+    hipLaunchKernelGGL(k_adam_pt_batched, dim3(static_cast<uint32_t>(ab + pb)), dim3(256), 0, s, b);
     if ((st = check_launch("Adam and P^T staging"))) return st;
+    i0 += k;
   }
   if (dtype != COMPACT_BF16) return COMPACT_OK;
-  static_assert(kDecBatch >= kStepBatch, "one decompression launch per Adam launch");
-  for (int i0 = 0; i0 < count; i0 += per) {
+  for (int64_t i0 = 0; i0 < count;) {
     DecW4Batch d{};
-    d.count = std::min(per, count - i0);
-    d.begin[0] = 0;
-    for (int j = 0; j < d.count; ++j) {
-      d.layer[j] = plans[i0 + j].dl;
-      d.begin[j + 1] = d.begin[j] + plans[i0 + j].dec_tiles;
+    d.ws = static_cast<char*>(ws);
+    const int64_t k = take_layers(plans, i0, even_share(count, kDecBatch), false, d.shape, d.shape_of);
+    d.count = static_cast<int>(k);
+    for (int64_t j = 0; j < k; ++j) {
+      const StepPlan& P = plans[i0 + j];
+      d.W[j] = P.W;
+      d.base[j] = static_cast<uint32_t>(P.offset / kWsAlign);
+      d.coef[j] = P.coef;
+      d.begin[j + 1] = d.begin[j] + static_cast<int>(P.dec_tiles);
     }
     const hipError_t e = dec_w4_launch(d, w_dtype == COMPACT_F32, s);
     if (e != hipSuccess) return fail(COMPACT_EHIP, "decompression launch: %s", hipGetErrorString(e));
+    i0 += k;
   }
   return COMPACT_OK;
 }
@@ -1175,20 +1194,21 @@ int compact_step(void* W, int64_t ldw, const float* G, float* M, float* V, int64
   const size_t need = compact_step_workspace_bytes(n, m, r, dtype);
   if (ws == nullptr || ws_bytes < need) return fail(COMPACT_EWORKSPACE, "step workspace %zu B < %zu B", ws_bytes, need);
   hipStream_t s = static_cast<hipStream_t>(stream);
+  void* base = align_ws(ws);
   std::vector<StepPlan> plans(1);
-  plan_step(W, ldw, G, M, V, n, m, r, seed, lr, alpha, proj, dtype, align_ws(ws), plans[0]);
-  if ((st = launch_step_groups(plans, adam_consts(t, beta1, beta2, eps, proj, dtype), dtype, w_dtype, s))) return st;
-  if (dtype == COMPACT_F32 && f32_fits({plans[0].al.ldn})) {
+  plan_step(W, ldw, G, M, V, n, m, r, seed, lr, alpha, proj, dtype, 0, plans[0]);
+  if ((st = launch_steps(plans, adam_consts(t, beta1, beta2, eps, proj, dtype), dtype, w_dtype, base, s))) return st;
+  if (dtype == COMPACT_F32 && f32_fits({n_ld(m)})) {
     PairF32 p{};
-    p.job[0] = f32_job(f32_pgen(seed, n, r, proj), f32_mat(plans[0].al.N, plans[0].al.ldn, m), n, m, r, W, ldw,
-                       plans[0].dl.coef, 1);
+    p.job[0] = f32_job(f32_pgen(seed, n, r, proj), f32_mat(base, n_ld(m), m), n, m, r, W, ldw,
+                       plans[0].coef, 1);
     if ((st = launch_f32<F32Wide, F32Wide, F32Narrow, F32Narrow>(k_dec_f32<false>, k_dec_f32<true>, p, s, "decompress (fp32)"))) return st;
   } else if (dtype == COMPACT_F32) {
     GemmF32Params gp{};
     gp.A = pgen_operand(seed, n, r, proj);
-    gp.B = mem_operand(static_cast<const float*>(plans[0].al.N), plans[0].al.ldn, 1, r, m);
+    gp.B = mem_operand(static_cast<const float*>(base), n_ld(m), 1, r, m);
     gp.M = n; gp.N = m; gp.K = r; gp.mode = 1;
-    gp.out = static_cast<float*>(W); gp.ldo = ldw; gp.coef = plans[0].dl.coef;
+    gp.out = static_cast<float*>(W); gp.ldo = ldw; gp.coef = plans[0].coef;
     if ((st = launch_gemm_f32(gp, s, "decompress (fp32)"))) return st;
   }
   return ok();
@@ -1220,13 +1240,14 @@ int compact_step_batched(const compact_layer* layers, int32_t count, int64_t t, 
   if (ws == nullptr || ws_bytes < need) return fail(COMPACT_EWORKSPACE, "batched step workspace %zu B < %zu B", ws_bytes, need);
   hipStream_t s = static_cast<hipStream_t>(stream);
   std::vector<StepPlan> plans(static_cast<size_t>(count));
-  char* cursor = static_cast<char*>(align_ws(ws));
+  size_t offset = 0;
   for (int32_t i = 0; i < count; ++i) {
     const compact_layer& L = layers[i];
-    plan_step(L.W, L.ldw, L.G, L.M, L.V, L.n, L.m, L.r, L.seed, lr, L.alpha, proj, dtype, cursor, plans[i]);
-    cursor += step_layer_bytes(L.n, L.m, L.r, dtype);
+    plan_step(L.W, L.ldw, L.G, L.M, L.V, L.n, L.m, L.r, L.seed, lr, L.alpha, proj, dtype, offset, plans[i]);
+    offset += step_layer_bytes(L.n, L.m, L.r, dtype);
   }
-  if ((st = launch_step_groups(plans, adam_consts(t, beta1, beta2, eps, proj, dtype), dtype, w_dtype, s))) return st;
+  if ((st = launch_steps(plans, adam_consts(t, beta1, beta2, eps, proj, dtype), dtype, w_dtype, align_ws(ws), s)))
+    return st;
   return ok();
 }
 

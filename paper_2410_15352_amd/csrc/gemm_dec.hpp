@@ -39,7 +39,7 @@ constexpr int kDecAhead = kDecStages - 1;             // K steps copied ahead
 constexpr uint32_t kDecStage = kDecK * kDecT * 2;     // 4 KB, one operand
 constexpr uint32_t kDecBBase = kDecStages * kDecStage;
 constexpr size_t kDecLds = 2u * kDecStages * kDecStage;  // 32 KB
-constexpr int kDecBatch = 40;                         // layers per launch
+constexpr int kDecBatch = 180;                        // layers per launch
 
 struct DecW4Layer {
   void* W;              // [n x m], ld ldw; bf16 or fp32 (the launch's w_f32)
@@ -53,10 +53,29 @@ struct DecW4Layer {
 
 struct DecW4Batch {
   int count;
+  char* ws;
+  StepShape shape[kStepShapes];
+  void* W[kDecBatch];
+  uint32_t base[kDecBatch];  // scratch of the layer (N, then P^T): ws + 256 base
+  float coef[kDecBatch];
   int begin[kDecBatch + 1];  // first workgroup of each layer; begin[count] = grid
-  DecW4Layer layer[kDecBatch];
+  uint8_t shape_of[kDecBatch];
 };
 static_assert(sizeof(DecW4Batch) <= 4096, "kernel argument size");
+
+__device__ __forceinline__ DecW4Layer dec_layer(const DecW4Batch& d, int l) {
+  const StepShape& sh = d.shape[d.shape_of[l]];
+  const char* base = d.ws + int64_t(256) * d.base[l];
+  DecW4Layer p;
+  p.W = d.W[l];
+  p.N = reinterpret_cast<const uint16_t*>(base);
+  p.pt = reinterpret_cast<const uint16_t*>(base + step_n_bytes(sh.m, sh.r, 2));
+  p.ldw = sh.ldw; p.ldn = static_cast<int>(step_ldn(sh.m)); p.ldpt = static_cast<int>(step_ldpt(sh.n));
+  p.n = sh.n; p.m = sh.m; p.r = sh.r;
+  p.tiles_c = (sh.m + kDecT - 1) / kDecT;
+  p.coef = d.coef[l];
+  return p;
+}
 
 // s_waitcnt vmcnt(N) lgkmcnt(0), then s_barrier.
 template <int N>

@@ -35,21 +35,34 @@ struct AdamLayer {
   float* M;
   float* V;
   void* N;
-  uint16_t* pt;  // P^T panel [r][ldpt], or null
+  uint16_t* pt;  // P^T panel [r][ldpt]
   PhiloxKey key;
   int ldn, r, m;
   int ldpt, n;
 };
 
-constexpr int kStepBatch = 40;  // layers per launch (kernel argument size)
+// Layers per launch.  A launch's first and last wave of workgroups leave CUs idle
+// for some microseconds, so the fewer launches the better, and a layer table in the
+// kernel's arguments (4096 bytes) holds what cannot be derived only: pointers, the
+// key, the offset of the layer's scratch, and sizes once per distinct shape.  (40
+// layers per launch, sizes and derived pointers in the table: 43 us per launch, five
+// for the 168 layers of LLaMA-350M; 84 per launch: two of 89 us.)
+constexpr int kStepBatch = 84;
 constexpr int kAdamVec = 4;     // float4 groups per thread
 
 struct StepBatch {
   AdamConsts c;
   int count;
+  char* ws;
+  StepShape shape[kStepShapes];
+  const float* G[kStepBatch];
+  float* M[kStepBatch];
+  float* V[kStepBatch];
+  PhiloxKey key[kStepBatch];
+  uint32_t base[kStepBatch];       // scratch of the layer: ws + 256 base
   int adam_begin[kStepBatch + 1];  // first Adam workgroup of each layer
   int pt_begin[kStepBatch + 1];    // first P^T workgroup of each layer
-  AdamLayer layer[kStepBatch];
+  uint8_t shape_of[kStepBatch];
 };
 static_assert(sizeof(StepBatch) <= 4096, "kernel argument size");
 
@@ -207,14 +220,21 @@ __global__ void k_adam_pt_batched(StepBatch s) {
   const int before = static_cast<int>(b * na / total);
   const bool adam = static_cast<int>((b + 1) * na / total) > before;
   const int idx = adam ? before : static_cast<int>(b) - before;
+  const int l = batch_layer_of(adam ? s.adam_begin : s.pt_begin, s.count, idx);
+  const StepShape& sh = s.shape[s.shape_of[l]];
+  AdamLayer p;
+  p.G = s.G[l]; p.M = s.M[l]; p.V = s.V[l];
+  char* base = s.ws + int64_t(256) * s.base[l];
+  p.N = base;
+  p.pt = reinterpret_cast<uint16_t*>(base + step_n_bytes(sh.m, sh.r, s.c.n_f32 ? 4 : 2));
+  p.key = s.key[l];
+  p.ldn = static_cast<int>(step_ldn(sh.m)); p.r = sh.r; p.m = sh.m;
+  p.ldpt = static_cast<int>(step_ldpt(sh.n)); p.n = sh.n;
   if (adam) {
-    const int l = batch_layer_of(s.adam_begin, s.count, idx);
     const int nb = s.adam_begin[l + 1] - s.adam_begin[l];
-    adam_range(s.layer[l], s.c, static_cast<int64_t>(idx - s.adam_begin[l]) * blockDim.x + threadIdx.x,
+    adam_range(p, s.c, static_cast<int64_t>(idx - s.adam_begin[l]) * blockDim.x + threadIdx.x,
                static_cast<int64_t>(nb) * blockDim.x);
   } else {
-    const int l = batch_layer_of(s.pt_begin, s.count, idx);
-    const AdamLayer& p = s.layer[l];
     const int64_t u = static_cast<int64_t>(idx - s.pt_begin[l]) * blockDim.x + threadIdx.x;
     if (u >= proj_t_units(s.c.kind, p.r, p.ldpt)) return;
     proj_t_unit(ProjDesc{s.c.kind, p.r, s.c.sparse_s}, p.key, p.n, 1.0f, PanelOut{p.pt, p.ldpt, 0}, 0, p.ldpt, u);

@@ -30,7 +30,7 @@ template <bool WF32>
 __global__ __launch_bounds__(256, WF32 ? 2 : 4) void k_dec_w4(DecW4Batch d) {
   const int b = static_cast<int>(xcd_remap(blockIdx.x, gridDim.x));
   const int l = batch_layer_of(d.begin, d.count, b);
-  dec_w4_tile<WF32>(d.layer[l], b - d.begin[l]);
+  dec_w4_tile<WF32>(dec_layer(d, l), b - d.begin[l]);
 }
 
 namespace {
