@@ -71,6 +71,12 @@ struct StepShape {
   int n, m, r, ldw;
 };
 
+// Shape index of layer l, four to a word (a byte array would be read through the
+// vector memory path, at the head of every workgroup).
+__host__ __device__ inline int shape_index(const uint32_t* words, int l) {
+  return static_cast<int>((words[l >> 2] >> (8 * (l & 3))) & 0xFFu);
+}
+
 // Scratch of a layer: N [r][round_up(m, 8)], then (bf16) P^T [r][round_up(n, 64)],
 // each on a 256-byte boundary.
 __host__ __device__ inline int64_t step_ldn(int64_t m) { return round_up(m, 8); }

@@ -1108,9 +1108,9 @@ void plan_step(void* W, int64_t ldw, const float* G, float* M, float* V, int64_t
 
 // The layers of one launch's table: as many of plans[i0 ..] as hold at most
 // `max_layers` layers, kStepShapes distinct shapes and 2^30 workgroups.  Fills
-// the table's shapes and each layer's shape index.
+// the table's shapes and each layer's shape index (zero on entry).
 int64_t take_layers(const std::vector<StepPlan>& plans, int64_t i0, int64_t max_layers, bool adam,
-                    StepShape* shape, uint8_t* shape_of) {
+                    StepShape* shape, uint32_t* shape_of) {
   int shapes = 0;
   int64_t k = 0, blocks = 0;
   const int64_t left = static_cast<int64_t>(plans.size()) - i0;
@@ -1126,7 +1126,7 @@ int64_t take_layers(const std::vector<StepPlan>& plans, int64_t i0, int64_t max_
       if (shapes == kStepShapes) break;
       shape[shapes++] = P.shape;
     }
-    shape_of[k] = static_cast<uint8_t>(f);
+    shape_of[k >> 2] |= static_cast<uint32_t>(f) << (8 * (k & 3));
   }
   return k;
 }

@@ -9,8 +9,11 @@
 // is done on the accumulators in registers (no LDS).  bf16 W: an 8 x 8
 // transpose across lanes (DPP) turns the MFMA output layout into rows, so that
 // each lane reads and writes 8 consecutive columns (one 16-byte access; 8 loads
-// and 8 stores per lane and tile instead of 32 + 32).  fp32 W: one DPP swap
-// between adjacent lanes gives pairs of two columns.
+// and 8 stores per lane and tile instead of 32 + 32); a swap of lane halves
+// (v_permlane32_swap) between the two column blocks then gives an access
+// instruction 8 row segments of 128 bytes, whole cache lines, instead of 16 of 64
+// (step of LLaMA-350M: 548 -> 539 us).  fp32 W: one DPP swap between adjacent
+// lanes gives pairs of two columns.
 //
 // Workgroup: 4 waves, each 64 (columns of W) x 64 (rows of W) = 2 x 2 MFMA
 // 32x32x16 fragments.  Both operands are K-row major (N [r][m], P^T [r][n]); they
@@ -59,12 +62,12 @@ struct DecW4Batch {
   uint32_t base[kDecBatch];  // scratch of the layer (N, then P^T): ws + 256 base
   float coef[kDecBatch];
   int begin[kDecBatch + 1];  // first workgroup of each layer; begin[count] = grid
-  uint8_t shape_of[kDecBatch];
+  uint32_t shape_of[(kDecBatch + 3) / 4];  // shape_index
 };
 static_assert(sizeof(DecW4Batch) <= 4096, "kernel argument size");
 
 __device__ __forceinline__ DecW4Layer dec_layer(const DecW4Batch& d, int l) {
-  const StepShape& sh = d.shape[d.shape_of[l]];
+  const StepShape& sh = d.shape[shape_index(d.shape_of, l)];
   const char* base = d.ws + int64_t(256) * d.base[l];
   DecW4Layer p;
   p.W = d.W[l];
@@ -123,6 +126,14 @@ __device__ __forceinline__ void dec_transpose8(float (&x)[8], int lane) {
   }
 }
 
+// Lanes 32 .. 63 of a take lanes 0 .. 31 of b, and lanes 0 .. 31 of b take lanes
+// 32 .. 63 of a.
+__device__ __forceinline__ void dec_swap_halves(float& a, float& b) {
+  const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(v[0]);
+  b = __uint_as_float(v[1]);
+}
+
 template <bool WF32>
 __device__ __forceinline__ void dec_w4_tile(const DecW4Layer& p, int tile) {
   typedef typename std::conditional<WF32, u32x2, uint32_t>::type WVec;
@@ -169,12 +180,13 @@ __device__ __forceinline__ void dec_w4_tile(const DecW4Layer& p, int tile) {
                                             view_bytes(p.n, p.m, p.ldw, i0, c0, kEsz));
   const int odd = lane & 1;
   const int row_l = wi * 64 + 4 * (lane >> 5) + 2 * odd, col_l = wc * 64 + (lane & 30);
-  // bf16 W in rows: lane (l / 32, c = (l % 32) / 8, t = l % 8) holds, for block
-  // (b, a) and half s, row wi 64 + 32 b + 16 s + 8 (t / 4) + 4 (l / 32) + t % 4
-  // and the 8 columns wc 64 + 32 a + 8 c .. + 7 (one 16-byte access); the
-  // accumulators reach that layout through an 8 x 8 transpose across lanes
-  const int tr = lane & 7, row_r = wi * 64 + 8 * (tr >> 2) + 4 * (lane >> 5) + (tr & 3);
-  const int col_r = wc * 64 + 8 * ((lane & 31) >> 3);
+  // bf16 W in rows: lane (l / 32, c = (l % 32) / 8, t = l % 8) holds, for row block b,
+  // half s and k = 0, 1, row wi 64 + 32 b + 16 s + 8 (t / 4) + 4 k + t % 4 and the 8
+  // columns wc 64 + 32 (l / 32) + 8 c .. + 7: an access instruction covers 8 row
+  // segments of 128 bytes.  The accumulators reach that layout through an 8 x 8
+  // transpose across lanes and a swap of lane halves between the two column blocks
+  const int tr = lane & 7, row_r = wi * 64 + 8 * (tr >> 2) + (tr & 3);
+  const int col_r = wc * 64 + 8 * (lane >> 3);
   f32x16 acc[2][2];  // [b][a]
   const f32x16 zero = {};
 #pragma unroll
@@ -219,11 +231,11 @@ __device__ __forceinline__ void dec_w4_tile(const DecW4Layer& p, int tile) {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int sh = 0; sh < 2; ++sh)
 #pragma unroll
-        for (int sh = 0; sh < 2; ++sh) {
-          const int off = ((row_r + b * 32 + 16 * sh) * p.ldw + col_r + a * 32) * 2;
-          wr[b][a][sh] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, off, 0, 0));
+        for (int k = 0; k < 2; ++k) {
+          const int off = ((row_r + b * 32 + 16 * sh + 4 * k) * p.ldw + col_r) * 2;
+          wr[b][sh][k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, off, 0, 0));
         }
   }
 
@@ -236,33 +248,39 @@ __device__ __forceinline__ void dec_w4_tile(const DecW4Layer& p, int tile) {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int sh = 0; sh < 2; ++sh) {
+        float x[2][8];  // by column block, then by k
 #pragma unroll
-        for (int sh = 0; sh < 2; ++sh) {
-          float x[8];
+        for (int a = 0; a < 2; ++a) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] = coef * acc[b][a][8 * sh + e];
-          dec_transpose8(x, lane);  // x[u] = column col_r + 32 a + u of this lane's row
-          const u32x4 w = wr[b][a][sh];
+          for (int e = 0; e < 8; ++e) x[a][e] = coef * acc[b][a][8 * sh + e];
+          dec_transpose8(x[a], lane);  // x[a][u] = column wc 64 + 32 a + 8 c + u of this lane's row
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) dec_swap_halves(x[0][u], x[1][u]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const u32x4 w = wr[b][sh][k];
           u32x4 o;
 #pragma unroll
-          for (int k = 0; k < 4; ++k)
-            o[k] = pack_bf16x2(__uint_as_float(w[k] << 16) - x[2 * k], __uint_as_float(w[k] & 0xFFFF0000u) - x[2 * k + 1]);
-          const int col = col_r + a * 32;
-          const int off = ((row_r + b * 32 + 16 * sh) * p.ldw + col) * 2;
-          if (col + 8 <= m_left) {
+          for (int q = 0; q < 4; ++q)
+            o[q] = pack_bf16x2(__uint_as_float(w[q] << 16) - x[k][2 * q],
+                               __uint_as_float(w[q] & 0xFFFF0000u) - x[k][2 * q + 1]);
+          const int off = ((row_r + b * 32 + 16 * sh + 4 * k) * p.ldw + col_r) * 2;
+          if (col_r + 8 <= m_left) {
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(f32x4, o), rw, off, 0, 0);
-          } else if (col < m_left) {
+          } else if (col_r < m_left) {
             // the tile's last columns: whole pairs, then a last single column
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              if (col + 2 * k + 2 <= m_left)
-                __builtin_amdgcn_raw_buffer_store_b32(o[k], rw, off + 4 * k, 0, 0);
-              else if (col + 2 * k < m_left)
-                __builtin_amdgcn_raw_buffer_store_b16(static_cast<unsigned short>(o[k]), rw, off + 4 * k, 0, 0);
+            for (int q = 0; q < 4; ++q) {
+              if (col_r + 2 * q + 2 <= m_left)
+                __builtin_amdgcn_raw_buffer_store_b32(o[q], rw, off + 4 * q, 0, 0);
+              else if (col_r + 2 * q < m_left)
+                __builtin_amdgcn_raw_buffer_store_b16(static_cast<unsigned short>(o[q]), rw, off + 4 * q, 0, 0);
             }
           }
         }
+      }
     return;
   }
 #pragma unroll

@@ -44,9 +44,10 @@ struct AdamLayer {
 // Layers per launch.  A launch's first and last wave of workgroups leave CUs idle
 // for some microseconds, so the fewer launches the better, and a layer table in the
 // kernel's arguments (4096 bytes) holds what cannot be derived only: pointers, the
-// key, the offset of the layer's scratch, and sizes once per distinct shape.  (40
-// layers per launch, sizes and derived pointers in the table: 43 us per launch, five
-// for the 168 layers of LLaMA-350M; 84 per launch: two of 89 us.)
+// key, the offset of the layer's scratch, and sizes once per distinct shape.  (The
+// 168 layers of LLaMA-350M: five Adam launches of 43 us and five decompression
+// launches of 78 us with 40 layers each; two and one launch, the whole step 603 ->
+// 548 us.)
 constexpr int kStepBatch = 84;
 constexpr int kAdamVec = 4;     // float4 groups per thread
 
@@ -62,7 +63,7 @@ struct StepBatch {
   uint32_t base[kStepBatch];       // scratch of the layer: ws + 256 base
   int adam_begin[kStepBatch + 1];  // first Adam workgroup of each layer
   int pt_begin[kStepBatch + 1];    // first P^T workgroup of each layer
-  uint8_t shape_of[kStepBatch];
+  uint32_t shape_of[(kStepBatch + 3) / 4];  // shape_index
 };
 static_assert(sizeof(StepBatch) <= 4096, "kernel argument size");
 
@@ -221,7 +222,7 @@ __global__ void k_adam_pt_batched(StepBatch s) {
   const bool adam = static_cast<int>((b + 1) * na / total) > before;
   const int idx = adam ? before : static_cast<int>(b) - before;
   const int l = batch_layer_of(adam ? s.adam_begin : s.pt_begin, s.count, idx);
-  const StepShape& sh = s.shape[s.shape_of[l]];
+  const StepShape& sh = s.shape[shape_index(s.shape_of, l)];
   AdamLayer p;
   p.G = s.G[l]; p.M = s.M[l]; p.V = s.V[l];
   char* base = s.ws + int64_t(256) * s.base[l];
