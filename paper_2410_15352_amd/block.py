@@ -85,7 +85,7 @@ class DenseLinear(torch.nn.Module):
         self.weight = torch.nn.Parameter(weight)
 
     def forward(self, x):
-        return (x.reshape(-1, x.shape[-1]) @ self.weight).reshape(*x.shape[:-1], self.weight.shape[1])
+        return ops.dense(x.reshape(-1, x.shape[-1]), self.weight).reshape(*x.shape[:-1], self.weight.shape[1])
 
 
 class LlamaBlock(torch.nn.Module):
