@@ -15,6 +15,7 @@ no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 
 from . import _lib
 
@@ -86,6 +87,9 @@ def _stream(stream, ref):
     import torch
     if stream is not None:
         return stream
+    if ref.is_cuda:
+        # the handle alone: torch.cuda.current_stream builds a Stream object each time
+        return torch._C._cuda_getCurrentRawStream(ref.device.index)
     return torch.cuda.current_stream(ref.device).cuda_stream
 
 
@@ -129,19 +133,30 @@ def compact_fwd(x, W, y, z, seed, proj="gaussian", ws=None, stream=None):
     _check("compact_fwd", st)
 
 
+# A training loop marshals the same few sizes on every call: the arrays (only read
+# by the library) and the workspace sizes are kept by value, 256 of each.
+@functools.lru_cache(maxsize=256)
+def _size_arrays(ms, rs):
+    return (ctypes.c_int64 * len(ms))(*ms), (ctypes.c_int64 * len(rs))(*rs)
+
+
 def _group_arrays(ms, rs, seeds=None):
     count = len(ms)
     if len(rs) != count or (seeds is not None and len(seeds) != count):
         raise ValueError("one m, r (and seed) per projection")
-    m_arr = (ctypes.c_int64 * count)(*[int(v) for v in ms])
-    r_arr = (ctypes.c_int64 * count)(*[int(v) for v in rs])
+    m_arr, r_arr = _size_arrays(tuple(map(int, ms)), tuple(map(int, rs)))
     s_arr = None if seeds is None else (ctypes.c_uint64 * count)(*[int(v) & (2**64 - 1) for v in seeds])
     return count, m_arr, r_arr, s_arr
 
 
-def fwd_group_workspace_bytes(n, ms, rs, dtype=BF16):
+@functools.lru_cache(maxsize=256)
+def _fwd_group_ws(n, ms, rs, dtype):
     count, m_arr, r_arr, _ = _group_arrays(ms, rs)
-    return int(_lib.load().compact_fwd_group_workspace_bytes(int(n), count, m_arr, r_arr, dtype))
+    return int(_lib.load().compact_fwd_group_workspace_bytes(n, count, m_arr, r_arr, dtype))
+
+
+def fwd_group_workspace_bytes(n, ms, rs, dtype=BF16):
+    return _fwd_group_ws(int(n), tuple(map(int, ms)), tuple(map(int, rs)), dtype)
 
 
 def compact_fwd_group(x, W, y, z, ms, rs, seeds, proj="gaussian", ws=None, stream=None):
@@ -189,9 +204,14 @@ def compact_bwd_noalloc(dy, W, z, dx, G, stream=None):
     _check("compact_bwd_noalloc", st)
 
 
-def bwd_group_workspace_bytes(tokens, n, ms, rs, dtype=BF16):
+@functools.lru_cache(maxsize=256)
+def _bwd_group_ws(tokens, n, ms, rs, dtype):
     count, m_arr, r_arr, _ = _group_arrays(ms, rs)
-    return int(_lib.load().compact_bwd_group_workspace_bytes(int(tokens), int(n), count, m_arr, r_arr, dtype))
+    return int(_lib.load().compact_bwd_group_workspace_bytes(tokens, n, count, m_arr, r_arr, dtype))
+
+
+def bwd_group_workspace_bytes(tokens, n, ms, rs, dtype=BF16):
+    return _bwd_group_ws(int(tokens), int(n), tuple(map(int, ms)), tuple(map(int, rs)), dtype)
 
 
 def compact_bwd_group(dy, W, z, dx, Gs, ms, rs, ws=None, stream=None, accumulate=False):

@@ -64,7 +64,7 @@ def _call(name, *args):
 
 
 def _stream(t):
-    return torch.cuda.current_stream(t.device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(t.device.index)
 
 
 def _plain(t):
@@ -77,11 +77,16 @@ def usable(*tensors):
         return False
     if torch._C._functorch.peek_interpreter_stack() is not None or torch.autograd.forward_ad._current_level >= 0:
         return False
+    dev = None
     for t in tensors:
         if not (_plain(t) and t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.numel() > 0
                 and t.data_ptr() % 16 == 0):
             return False
-    return all(t.device.index == torch.cuda.current_device() for t in tensors)
+        if dev is None:
+            dev = torch._C._cuda_getDevice()
+        if t.get_device() != dev:
+            return False
+    return True
 
 
 def norm_usable(x, g, *rest):
