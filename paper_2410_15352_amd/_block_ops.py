@@ -2,8 +2,8 @@
 RMSNorm with its residual, SwiGLU and the mean cross-entropy.
 
 They take dense bf16 tensors on the current GPU; `usable` says whether a call may
-go that way.  Everything else (CPU, other types and strides, tracing, functorch,
-forward-mode AD) takes the torch expressions beside each function, and so does a
+go that way.  Everything else (CPU, other types and strides, autocast, tracing,
+functorch, forward-mode AD) takes the torch expressions beside each function, and so does a
 backward that is itself recorded (create_graph=True)."""
 from __future__ import annotations
 
@@ -15,6 +15,7 @@ from . import _lib, bwd_workspace_bytes, compact_bwd
 
 _vp, _i64, _i32, _f32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_float
 RMSNORM_MAX_D = 4096
+MAX_ROWS = 1 << 24  # one workgroup of 256 threads per row at most: a launch has under 2^32 threads
 IGNORE = -100  # F.cross_entropy's default ignore_index
 
 
@@ -72,8 +73,11 @@ def _plain(t):
 
 
 def usable(*tensors):
-    """Dense bf16 tensors on the current device, outside every kind of tracing."""
+    """Dense bf16 tensors on the current device, outside autocast and every kind of
+    tracing."""
     if torch.compiler.is_compiling() or torch.jit.is_tracing() or torch._C._len_torch_dispatch_stack() > 0:
+        return False
+    if torch.is_autocast_enabled("cuda"):
         return False
     if torch._C._functorch.peek_interpreter_stack() is not None or torch.autograd.forward_ad._current_level >= 0:
         return False
@@ -90,7 +94,10 @@ def usable(*tensors):
 
 
 def norm_usable(x, g, *rest):
-    return x.dim() >= 1 and x.shape[-1] % 8 == 0 and 8 <= x.shape[-1] <= RMSNORM_MAX_D and usable(x, g, *rest)
+    """Rows of x with one gain per element (other gains broadcast or are refused by torch)."""
+    if x.dim() < 1 or x.shape[-1] % 8 != 0 or not 8 <= x.shape[-1] <= RMSNORM_MAX_D or g.shape != x.shape[-1:]:
+        return False
+    return x.numel() // x.shape[-1] < MAX_ROWS and usable(x, g, *rest)
 
 
 def _grad(t):
@@ -322,6 +329,6 @@ class _CrossEntropyFn(torch.autograd.Function):
 def cross_entropy(logits, targets):
     """F.cross_entropy(logits.float(), targets) for 2-D logits and class targets."""
     if (logits.dim() == 2 and _plain(targets) and targets.dtype == torch.int64 and targets.dim() == 1
-            and targets.shape[0] == logits.shape[0] and targets.device == logits.device and usable(logits)):
+            and targets.shape[0] == logits.shape[0] < MAX_ROWS and targets.device == logits.device and usable(logits)):
         return _CrossEntropyFn.apply(logits, targets.contiguous())
     return torch.nn.functional.cross_entropy(logits.float(), targets)

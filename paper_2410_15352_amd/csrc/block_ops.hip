@@ -353,12 +353,13 @@ __global__ __launch_bounds__(1024) void k_ce_mean(CeArgs a) {
   }
 }
 
-// dx = (softmax(x) - onehot(target)) dloss / count; zero for ignored rows.
+// dx = (softmax(x) - onehot(target)) dloss / count; zero for ignored rows, NaN (as
+// the loss) for a target outside 0 .. V - 1.
 __global__ __launch_bounds__(256) void k_ce_bwd(CeGradArgs a) {
   const int64_t row = blockIdx.x, begin = row * a.V, end = begin + a.V, total = a.rows * a.V;
   const int64_t t = a.target[row];
   const bool ignored = t == a.ignore_index;
-  const float lse = a.lse[row], scale = ignored ? 0.0f : a.dloss[0] / a.count[0];
+  const float lse = t >= 0 && t < a.V ? a.lse[row] : __builtin_nanf(""), scale = ignored ? 0.0f : a.dloss[0] / a.count[0];
   for (int64_t q = begin / 8 + threadIdx.x; q * 8 < end; q += 256) {
     Chunk c = ce_chunk(a.x, q, begin, end, total);
 #pragma unroll

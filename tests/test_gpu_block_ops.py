@@ -154,3 +154,39 @@ def test_split_qkv(b, l, heads, hd):
     qkv.grad = None
     ops.split_qkv(qkv)[1].backward(dense[1])  # only k is used
     assert torch.equal(qkv.grad[:, :, 1], dense[1].transpose(1, 2)) and not qkv.grad[:, :, 0::2].any()
+
+
+@pytest.mark.parametrize("rows,n,m", [(4096, 8, 16), (4096, 512, 520), (5003, 1024, 1024), (4097, 2048, 2048),
+                                      (4095, 512, 512), (4096, 2048, 2056), (4096, 12, 16)])  # the last three: the library
+def test_dense_weight_gradient(rows, n, m):
+    x, W, dy = _rand(rows, n).requires_grad_(True), _rand(n, m, seed=1), _rand(rows, m, seed=2)
+    W = torch.nn.Parameter(W)
+    y = ops.dense(x, W)
+    assert torch.equal(y, x.detach() @ W.detach())
+    own = rows >= 4096 and n % 8 == 0 and n * m <= 2048 * 2048
+    assert (type(y.grad_fn).__name__ == "_DenseFnBackward") == own
+    y.backward(dy)
+    assert torch.equal(x.grad, dy @ W.detach().t())
+    # fp32 sums over the rows: LAM sqrt(rows) roundings of the terms' sum, then one to bf16
+    X, D = x.detach().double(), dy.double()
+    _close(W.grad, X.t().contiguous() @ D, X.abs().t().contiguous() @ D.abs(), extra=LAM * U32 * rows ** 0.5)
+    W.grad = None
+    ops.dense(x.detach(), W).backward(dy[:1].expand(rows, m))  # a gradient that is not dense: the library
+    _close(W.grad, X.sum(0)[:, None] * D[:1], X.abs().sum(0)[:, None] * D[:1].abs(), extra=LAM * U32 * rows ** 0.5)
+
+
+def test_routes_that_stay_torch():
+    """A norm of another width is refused as before, autocast decides the types."""
+    norm, x = blk.RMSNorm(64), _rand(10, 128)
+    for call in (norm, norm.with_residual, lambda v: norm.add(v, v)):
+        with pytest.raises(RuntimeError):
+            call(x)
+    W = _rand(64, 64, seed=1)
+    x = _rand(4096, 64).requires_grad_(True)
+    with torch.autocast("cuda", dtype=torch.float16):
+        assert not ops.usable(x) and ops.dense(x, W).dtype == torch.float16
+    # a target that is no class: NaN in the loss and in its row's gradient
+    z = _rand(2, 40).requires_grad_(True)
+    loss = ops.cross_entropy(z, torch.tensor([40, 1], device=dev()))
+    loss.backward()
+    assert torch.isnan(loss) and torch.isnan(z.grad[0]).all()
