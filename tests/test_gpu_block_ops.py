@@ -99,7 +99,7 @@ def test_swiglu(rows, f):
         assert torch.equal(act.view(torch.int16), (torch.nn.functional.silu(gu[:, :f]) * gu[:, f:]).view(torch.int16))
 
 
-@pytest.mark.parametrize("rows,V", [(1, 1), (2, 7), (3, 1003), (64, 1000), (130, 32000), (1025, 2049), (5, 4104)])
+@pytest.mark.parametrize("rows,V", [(1, 1), (2, 7), (3, 1003), (64, 1000), (130, 32000), (1025, 2049), (5, 4104), (5, 12301)])
 def test_cross_entropy(rows, V):
     x = _rand(rows, V, scale=3.0).requires_grad_(True)
     t = torch.randint(V, (rows,), device=dev())
