@@ -344,13 +344,13 @@ W4Seg w4_seg(void* c, int64_t ld, int64_t cols) {
 
 // Which bf16 GEMM takes a product, given which of them can: kPersistent when
 // the persistent kernel is the better one, or when no tile kernel takes it.
-int choose_gemm(int64_t M, int64_t n0, int64_t n1, int64_t K, bool w4, bool tile, TileKind& kind) {
+int choose_gemm(int64_t M, int64_t n0, int64_t n1, int64_t K, bool w4, bool copies, bool tile, TileKind& kind) {
   kind = TileKind::kPersistent;
   if (!tile) return COMPACT_OK;
   int cus = 0;
   const hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return fail(COMPACT_EHIP, "device query: %s", hipGetErrorString(e));
-  kind = gemm_tile_choose(M, n0, n1, K, w4, cus);
+  kind = gemm_tile_choose(M, n0, n1, K, w4, copies, cus);
   return COMPACT_OK;
 }
 
@@ -585,8 +585,8 @@ int fwd_group_w4(const void* x, int64_t ldx, const void* W, int64_t ldw, void* y
       gemm_w4_eligible(tokens, n, ldx, ldb, rows_b, ldy, G.msum, gather ? 0 : ldz, gather ? 0 : G.rsum, true) &&
       tiled_fits(rows_b, n);
   TileKind kind = TileKind::kPersistent;
-  if ((st = choose_gemm(tokens, G.msum, gather ? 0 : G.rsum, n, w4, gemm_tile_eligible(tokens, n, ldx, ldb, rows_b),
-                        kind)))
+  if ((st = choose_gemm(tokens, G.msum, gather ? 0 : G.rsum, n, w4, false,
+                        gemm_tile_eligible(tokens, n, ldx, ldb, rows_b), kind)))
     return st;
   const bool tile = kind != TileKind::kPersistent;
   taken = ws != nullptr && (tile || w4);
@@ -875,7 +875,7 @@ int bwd_impl(const void* dy, int64_t lddy, const void* W, int64_t ldw, const voi
   const bool w4 = gemm_w4_eligible(tokens, m, lddy, ldw, n, lddx, n, 0, 0, stage_w);
   TileKind kind = TileKind::kPersistent;
   if (dx != nullptr &&
-      (st = choose_gemm(tokens, n, 0, m, w4, gemm_tile_eligible(tokens, m, lddy, ldw, n), kind)))
+      (st = choose_gemm(tokens, n, 0, m, w4, stage_w, gemm_tile_eligible(tokens, m, lddy, ldw, n), kind)))
     return st;
   if (dx != nullptr && kind != TileKind::kPersistent) {
     // a tile kernel reads W [n][m] as it is: one launch, no copy of W

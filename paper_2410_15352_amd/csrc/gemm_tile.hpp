@@ -227,8 +227,9 @@ constexpr int kTileKinds = 4;
 
 // The kernel that should compute an M x (n0 + n1) product over K (n1 = 0: one
 // output segment; each segment starts on a tile of its own); `persistent`: the
-// persistent kernel takes the shape.
-TileKind gemm_tile_choose(int64_t M, int64_t n0, int64_t n1, int64_t K, bool persistent, int cus);
+// persistent kernel takes the shape, `copies`: after a K-tiled copy of B that the
+// tile kernels do without.
+TileKind gemm_tile_choose(int64_t M, int64_t n0, int64_t n1, int64_t K, bool persistent, bool copies, int cus);
 
 // True when the tile kernels take this product: 32-bit buffer offsets inside a tile.
 bool gemm_tile_eligible(int64_t M, int64_t K, int64_t lda, int64_t ldb, int64_t rows_b);

@@ -43,32 +43,43 @@ const Variant& variant_of(int kind) {
   return v[kind];
 }
 
-// Time of a launch, in microseconds, from measurements on MI355X over 23 shapes
-// (256 to 32768 rows, 512 to 5728 columns, K 512 to 5472): the tiles run in
-// rounds of `slots` per CU; a 64-deep K step of a round takes `alone` with few
-// workgroups on the chip and `full` with all slots taken (the copies then share
-// L2), a round `ov` more (first copies and output), the launch `base`.  Over many
-// rounds, or with several workgroups per CU, a CU takes the next tile when it is
-// free and a part of a round costs its part; otherwise the last round lasts as long
-// as a tile.  The persistent kernel deals its tiles out beforehand (always the
-// latter).
+// Time of a launch, in microseconds, fitted to measurements on MI355X (67 products
+// of 200 to 65000 rows, 266 to 5461 columns, K 320 to 32000; a kernel's error is 8 to
+// 10% rms, the choice on average 0.4% from the best of the five and never more than
+// 1% slower than the persistent kernel).  The tiles run in rounds of `slots` per CU,
+// a last round of c tiles per CU lasting as long as its fullest CU: a 64-deep K step
+// with c tiles on a CU takes alone[c - 1] with few CUs at work and full[c - 1] with
+// all (the copies then share L2), a round `ov` more (first copies and output), the
+// launch `base`.  The persistent kernel's dL/dx first copies its N x K operand
+// (stage_cost); the forward stages its operand for either.
+// Counting parts of a round as their part took 5 to 15% longer than the persistent
+// kernel just past a whole round (26310 x 1254, K 1816: 168 us against 135).
 struct TileCost {
   int rows, cols, slots;
-  double alone, full, ov, base;
+  double base, ov, alone[3], full[3];
 };
 constexpr TileCost kCost[kTileKinds + 1] = {
-    {256, 128, 1, 0.57, 0.863, 5.6, 3.0}, {128, 128, 1, 0.35, 0.485, 3.2, 3.0}, {64, 128, 2, 0.21, 0.62, 2.0, 3.0},
-    {64, 64, 3, 0.14, 0.61, 1.2, 3.0},    {256, 256, 1, 1.08, 1.65, 4.0, 5.5},
+    {256, 128, 1, 0.0, 6.17, {0.519}, {1.007}},
+    {128, 128, 1, 1.24, 2.96, {0.340}, {0.603}},
+    {64, 128, 2, 2.19, 1.93, {0.229, 0.777}, {0.463, 0.709}},
+    {64, 64, 3, 3.53, 0.57, {0.198, 0.364, 1.071}, {0.258, 0.545, 0.703}},
+    {256, 256, 1, 8.1, 4.53, {0.931}, {1.687}},
 };
+
+double stage_cost(int64_t N, int64_t K) { return 1.65 + 1.58e-6 * double(N) * double(K); }
 
 double tile_cost(int k, int64_t M, int64_t n0, int64_t n1, int64_t K, int cus) {
   const TileCost& c = kCost[k];
-  const double tiles = double(ceil_div(M, c.rows)) * double(ceil_div(n0, c.cols) + ceil_div(n1, c.cols));
-  const double steps = double(ceil_div(K, 64)), per = double(cus) * c.slots, rounds = tiles / per;
-  if (k < kTileKinds && rounds > (c.slots > 1 ? 1.0 : 4.0)) return c.base + rounds * (c.ov + steps * c.full);
-  const double full = double(int64_t(rounds)), rest = tiles - full * per;
-  const double part = rest > 0 ? c.ov + steps * (c.alone + (c.full - c.alone) * rest / per) : 0.0;
-  return c.base + full * (c.ov + steps * c.full) + part;
+  const int64_t tiles = ceil_div(M, c.rows) * (ceil_div(n0, c.cols) + ceil_div(n1, c.cols)), per = int64_t(cus) * c.slots;
+  const double steps = double(ceil_div(K, 64));
+  const int64_t rounds = tiles / per, rest = tiles - rounds * per;
+  double t = c.base + double(rounds) * (c.ov + steps * c.full[c.slots - 1]);
+  if (rest > 0) {
+    const int64_t on = ceil_div(rest, cus);  // tiles on the fullest CU
+    const double busy = double(rest) / double(on * cus);
+    t += c.ov + steps * (c.alone[on - 1] + (c.full[on - 1] - c.alone[on - 1]) * busy);
+  }
+  return t;
 }
 
 }  // namespace
@@ -89,11 +100,19 @@ hipError_t device_cus(int* cus) {
   return hipSuccess;
 }
 
-// The cheapest kernel by the measured costs; a tile kernel has to win by 5%, about
-// the error of the estimate.
-TileKind gemm_tile_choose(int64_t M, int64_t n0, int64_t n1, int64_t K, bool persistent, int cus) {
+// The cheapest kernel by the measured costs; a tile kernel has to win by 3% (a third
+// of the estimate's error).  Where the persistent kernel does not
+// take the shape (K < 320, mostly), the other choice is the eight-wave kernel of 256 x
+// 256 tiles: the tile kernels are faster until its tiles fill the CUs (K 300, 700 + 150
+// columns: 5000 rows, 80 tiles, 22 -> 15 us; 12000 rows, 188 tiles, 25 us either way;
+// 30000 rows, 472 tiles, 43 against 46 us; K 256, 3072 + 64 columns, 65536 rows: 207
+// against 257 us).
+TileKind gemm_tile_choose(int64_t M, int64_t n0, int64_t n1, int64_t K, bool persistent, bool copies, int cus) {
+  if (!persistent && 10 * ceil_div(M, 256) * (ceil_div(n0, 256) + ceil_div(n1, 256)) > 7 * int64_t(cus))
+    return TileKind::kPersistent;
   int best = kTileKinds;
-  double t = persistent ? 0.95 * tile_cost(kTileKinds, M, n0, n1, K, cus) : HUGE_VAL;
+  double t = HUGE_VAL;
+  if (persistent) t = 0.97 * (tile_cost(kTileKinds, M, n0, n1, K, cus) + (copies ? stage_cost(n0, K) : 0.0));
   for (int k = 0; k < kTileKinds; ++k) {
     const double c = tile_cost(k, M, n0, n1, K, cus);
     if (c < t) {
