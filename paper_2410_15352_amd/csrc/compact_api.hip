@@ -480,6 +480,32 @@ int launch_f32(void (*fn)(PairF32), void (*fn_small)(PairF32), const PairF32& p,
   return launch_f32_tiles<Sm0, Sm1>(fn_small, one, s, what);
 }
 
+// W <- W - coef P N in tiles of 32 x 128 FN.  A workgroup generates its 32 columns of
+// P itself, so per K step it takes about kGen + FN (in units of a fragment's MFMAs,
+// 1024 clocks), and the CU with the most tiles sets the time (768 x 3072, r = 384:
+// 576, 288 and 192 tiles on 256 CUs take 44, 46 and 40 us; 768 x 768, where a CU has
+// one of any width, 20, 28 and 37).
+int launch_update_f32(const PairF32& p, hipStream_t s) {
+  int cus = 0;
+  const hipError_t e = device_cus(&cus);
+  if (e != hipSuccess) return fail(COMPACT_EHIP, "decompress (fp32): %s", hipGetErrorString(e));
+  constexpr int kGen = 2;  // (1.4 to 2.4 measured, by how well two tiles of a CU overlap)
+  int fn = 1;
+  int64_t best = 0;
+  for (int f = 1; f <= 3; ++f) {
+    const int64_t tiles = ceil_div(p.job[0].M, 32) * ceil_div(p.job[0].N, 128 * f);
+    const int64_t t = ceil_div(tiles, cus) * (kGen + f);
+    if (f == 1 || t < best) {
+      best = t;
+      fn = f;
+    }
+  }
+  const char* what = "decompress (fp32)";
+  if (fn == 1) return launch_f32_tiles<F32Update<1>, F32Update<1>>(k_dec_f32<1>, p, s, what);
+  if (fn == 2) return launch_f32_tiles<F32Update<2>, F32Update<2>>(k_dec_f32<2>, p, s, what);
+  return launch_f32_tiles<F32Update<3>, F32Update<3>>(k_dec_f32<3>, p, s, what);
+}
+
 OperandF32 mem_operand(const float* p, int64_t su, int64_t sv, int64_t U, int64_t V) {
   OperandF32 o{};
   o.p = p;
@@ -1202,7 +1228,7 @@ int compact_step(void* W, int64_t ldw, const float* G, float* M, float* V, int64
     PairF32 p{};
     p.job[0] = f32_job(f32_pgen(seed, n, r, proj), f32_mat(base, n_ld(m), m), n, m, r, W, ldw,
                        plans[0].coef, 1);
-    if ((st = launch_f32<F32Wide, F32Wide, F32Narrow, F32Narrow>(k_dec_f32<false>, k_dec_f32<true>, p, s, "decompress (fp32)"))) return st;
+    if ((st = launch_update_f32(p, s))) return st;
   } else if (dtype == COMPACT_F32) {
     GemmF32Params gp{};
     gp.A = pgen_operand(seed, n, r, proj);

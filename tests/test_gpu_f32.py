@@ -41,7 +41,8 @@ def _neighbours_untouched(v):
 # (T, n, m, r): one WG per 32 x 32 tile; just past tile edges; 64 x 64 tiles with a
 # small and a large G^; K just past, on and short of a K step
 CASES = [(1, 1, 1, 1), (31, 33, 65, 5), (33, 64, 32, 32), (257, 127, 129, 63), (700, 96, 480, 40),
-         (1025, 513, 1001, 65), (2047, 260, 1030, 130), (130, 1024, 3071, 512)]
+         (1025, 513, 1001, 65), (2047, 260, 1030, 130), (130, 1024, 3071, 512),
+         (64, 700, 2001, 30)]  # the last two: the update's tiles of 384 and 256 columns
 
 
 @pytest.mark.parametrize("proj", ["gaussian", "sparse-jl"])
