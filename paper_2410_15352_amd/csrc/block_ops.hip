@@ -12,8 +12,9 @@
 // bytes.  LLaMA-350M widths, 8192 tokens, MI355X: RMSNorm with the residual forward
 // 12 us, backward 16 + 5 us, SwiGLU 33 us (5.5 TB/s) and 44 us (6.1 TB/s), the
 // gradients of q, k, v joined 16 us; the block's forward and backward 1825 -> 1094
-// us.  Cross-entropy over 32000 logits: 108 us forward (4.9 TB/s; one chunk at a
-// time 148), 187 us (5.6 TB/s) backward, against 1.9 ms.
+// us.  Cross-entropy over 32000 logits: 108 us forward alone (4.9 TB/s; one
+// chunk at a time 141) and 140 us behind the GEMM that writes the logits (148),
+// backward 187 us (5.6 TB/s), against 1.9 ms for both.
 #include <hip/hip_runtime.h>
 
 #include "block_ops.hpp"
