@@ -19,6 +19,7 @@ save no activations and do not touch the linear layers.
 from __future__ import annotations
 
 import torch
+from torch.nn.modules import module as _module
 from torch.nn.attention import SDPBackend, sdpa_kernel
 
 from . import _block_ops as ops
@@ -60,19 +61,31 @@ class RMSNorm(torch.nn.Module):
             return ops.rmsnorm(x, self.weight, self.eps)
         return _RMSNormFn.apply(x, self.weight, self.eps)
 
+    def _plain(self):
+        """Calling this module runs the forward above and nothing else: no hook, no
+        other forward in its place, not compiled."""
+        return not (self._forward_hooks or self._forward_pre_hooks or self._backward_hooks or self._backward_pre_hooks
+                    or _module._global_forward_hooks or _module._global_forward_pre_hooks
+                    or _module._global_backward_hooks or _module._global_backward_pre_hooks
+                    or "forward" in vars(self) or type(self).forward is not _RMSNORM_FORWARD
+                    or self._compiled_call_impl is not None)
+
     def with_residual(self, x):
         """(x, norm(x)); the returned x is the one to add to later, so that both
         gradients of x are summed where the norm's is formed."""
-        if ops.norm_usable(x, self.weight):
+        if self._plain() and ops.norm_usable(x, self.weight):
             return ops.rmsnorm_residual(x, self.weight, self.eps)
-        return x, _RMSNormFn.apply(x, self.weight, self.eps)
+        return x, self(x)
 
     def add(self, x, o):
         """(x + o, norm(x + o))."""
-        if x.shape == o.shape and ops.norm_usable(x, self.weight, o):
+        if x.shape == o.shape and self._plain() and ops.norm_usable(x, self.weight, o):
             return ops.add_rmsnorm(x, o, self.weight, self.eps)
         s = x + o
-        return s, _RMSNormFn.apply(s, self.weight, self.eps)
+        return s, self(s)
+
+
+_RMSNORM_FORWARD = RMSNorm.forward
 
 
 class DenseLinear(torch.nn.Module):
@@ -124,14 +137,20 @@ class LlamaBlock(torch.nn.Module):
 
     def forward(self, x):
         b, l, d = x.shape
-        x, h = self.norm1.with_residual(x)
+        # (a norm that was replaced or subclassed is called as any module)
+        x, h = self.norm1.with_residual(x) if type(self.norm1) is RMSNorm else (x, self.norm1(x))
         qkv = self.qkv(h.reshape(b * l, d)).reshape(b, l, 3, self.heads, d // self.heads)
         # (three slices would each scatter into a zero-filled tensor of q|k|v's size
         # in the backward, which are then summed)
         q, k, v = ops.split_qkv(qkv)
         with sdpa_kernel([SDPBackend.FLASH_ATTENTION]):
             a = torch.nn.functional.scaled_dot_product_attention(q, k, v, is_causal=True)
-        x5, h2 = self.norm2.add(x, self.o(a.transpose(1, 2).reshape(b * l, d)).reshape(b, l, d))
+        o = self.o(a.transpose(1, 2).reshape(b * l, d)).reshape(b, l, d)
+        if type(self.norm2) is RMSNorm:
+            x5, h2 = self.norm2.add(x, o)
+        else:
+            x5 = x + o
+            h2 = self.norm2(x5)
         gu = self.gu(h2.reshape(b * l, d))
         return x5 + self.down(ops.swiglu(gu, self.ffn)).reshape(b, l, d)
 

@@ -19,3 +19,66 @@ def test_norm_takes_one_gain_per_element(monkeypatch, width, gains, takes):
 def test_norm_of_another_width_is_refused():
     with pytest.raises(RuntimeError):
         blk.RMSNorm(64)(torch.randn(3, 128).to(torch.bfloat16))
+
+
+def _block_on_cpu():
+    torch.manual_seed(0)
+    return blk.LlamaBlock(64, 1, 64, rank=None, device="cpu"), torch.randn(2, 8, 64).to(torch.bfloat16)
+
+
+def test_block_runs_its_norms_as_modules():
+    """Hooks on a block's norms run, and what a hook returns counts."""
+    b, x = _block_on_cpu()
+    calls, x = [], x.requires_grad_(True)
+    for norm in (b.norm1, b.norm2):
+        norm.register_forward_pre_hook(lambda m, a: calls.append("pre"))
+        norm.register_forward_hook(lambda m, a, out: calls.append("forward"))
+        norm.register_full_backward_hook(lambda m, gi, go: calls.append("backward"))
+    b(x).float().sum().backward()
+    assert calls.count("pre") == calls.count("forward") == calls.count("backward") == 2
+    b, x = _block_on_cpu()
+    y = b(x)
+    b.norm2.register_forward_hook(lambda m, a, out: 0 * out)  # no MLP
+    assert not torch.equal(b(x), y)
+    b.norm2._forward_hooks.clear()
+    assert torch.equal(b(x), y)
+
+
+@pytest.mark.parametrize("make", [torch.nn.Identity, lambda: torch.nn.LayerNorm(64, dtype=torch.bfloat16),
+                                  lambda: type("Sub", (blk.RMSNorm,), {"forward": lambda self, x: -x})(64, device="cpu")])
+def test_block_takes_replaced_norms(make):
+    b, x = _block_on_cpu()
+    b.norm1, b.norm2 = make(), make()
+    assert torch.isfinite(b(x)).all()
+
+
+def test_fused_norms_only_where_the_module_is_plain(monkeypatch):
+    """The kernels that join a norm with its residual take a norm without hooks."""
+    fused = []
+    monkeypatch.setattr(ops, "norm_usable", lambda *t: True)
+    monkeypatch.setattr(ops, "rmsnorm", lambda x, g, eps: blk._RMSNormFn.apply(x, g, eps))
+    monkeypatch.setattr(ops, "rmsnorm_residual", lambda x, g, eps: (fused.append(1), (x, blk._RMSNormFn.apply(x, g, eps)))[1])
+    monkeypatch.setattr(ops, "add_rmsnorm", lambda x, o, g, eps: (fused.append(2), (x + o, blk._RMSNormFn.apply(x + o, g, eps)))[1])
+
+    def routes(change, undo=lambda b: None):
+        b, x = _block_on_cpu()
+        change(b)
+        fused.clear()
+        try:
+            b(x)
+        finally:
+            undo(b)
+        return list(fused)
+
+    hook = lambda *a: None
+    handle = []
+    assert routes(lambda b: None) == [1, 2]
+    assert routes(lambda b: b.norm1.register_forward_hook(hook)) == [2]
+    assert routes(lambda b: b.norm2.register_forward_pre_hook(hook)) == [1]
+    assert routes(lambda b: b.norm2.register_full_backward_hook(hook)) == [1]
+    assert routes(lambda b: b.norm1.register_full_backward_pre_hook(hook)) == [2]
+    assert routes(lambda b: setattr(b.norm1, "forward", lambda x: x)) == [2]
+    assert routes(lambda b: handle.append(torch.nn.modules.module.register_module_forward_hook(hook)),
+                  lambda b: handle.pop().remove()) == []
+    monkeypatch.setattr(blk.RMSNorm, "forward", lambda self, x: x)
+    assert routes(lambda b: None) == []
