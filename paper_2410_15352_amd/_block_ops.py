@@ -4,7 +4,8 @@ RMSNorm with its residual, SwiGLU and the mean cross-entropy.
 They take dense bf16 tensors on the current GPU; `usable` says whether a call may
 go that way.  Everything else (CPU, other types and strides, autocast, tracing,
 functorch, forward-mode AD) takes the torch expressions beside each function, and so does a
-backward that is itself recorded (create_graph=True)."""
+backward that is itself recorded (create_graph=True) or batched (is_grads_batched=True), or that
+gets its saved tensors back from a hook in another type, layout or place."""
 from __future__ import annotations
 
 import ctypes
@@ -107,6 +108,32 @@ def _grad(t):
     return t if t.data_ptr() % 16 == 0 else t.clone()
 
 
+def _grads(saved, *grads):
+    """The gradients (None stays None) as a backward's kernel takes them, or None
+    where that kernel must not run: a backward that is recorded, or batched
+    (is_grads_batched), or whose saved tensors came back from a saved-tensor hook in
+    another type, layout or place."""
+    if torch.is_grad_enabled() or not usable(*saved) or not all(g is None or _plain(g) for g in grads):
+        return None
+    grads = [None if g is None else _grad(g) for g in grads]
+    return grads if usable(*(g for g in grads if g is not None)) else None
+
+
+def _companion(t, like, dtype, shape):
+    """A saved tensor beside the bf16 ones is still what the forward's kernel wrote or read."""
+    return (_plain(t) and t.dtype == dtype and tuple(t.shape) == tuple(shape) and t.is_contiguous()
+            and t.device == like.device)
+
+
+def _torch_grad(fn, x, dy):
+    """The gradient of the torch expression fn(x), itself differentiable where the
+    backward is recorded."""
+    recorded = torch.is_grad_enabled()
+    with torch.enable_grad():
+        x = x if recorded and x.requires_grad else x.detach().requires_grad_(True)
+        return torch.autograd.grad(fn(x), x, dy, create_graph=recorded)[0]
+
+
 # ------------------------------- RMSNorm -----------------------------------
 
 def rmsnorm_reference_grad(x, rstd, g, dy):
@@ -144,14 +171,16 @@ class _NormFn(torch.autograd.Function):
         x, rstd, g = ctx.saved_tensors
         if dy is None:
             return dres, dres if ctx.added else None, None, None
-        if torch.is_grad_enabled():
+        grads = None
+        if x.shape == dy.shape and g.shape == dy.shape[-1:] and _companion(rstd, x, torch.float32, dy.shape[:-1]):
+            grads = _grads((x, g), dy, dres)
+        if grads is None:
             dx, dg = rmsnorm_reference_grad(x, rstd, g, dy)
             dx = dx if dres is None else dx + dres
             return dx, dx if ctx.added else None, dg, None
+        dy, dres = grads
         d = x.shape[-1]
         rows = x.numel() // d
-        dy = _grad(dy)
-        dres = None if dres is None else _grad(dres)
         need = ctx.needs_input_grad[0] or ctx.needs_input_grad[1]
         dx = torch.empty_like(x) if need else None
         dg = torch.empty_like(g)
@@ -195,24 +224,26 @@ class _SwigluFn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dact):
         gu, s = ctx.saved_tensors
-        rows, f = s.shape
-        if torch.is_grad_enabled():
-            g, u = gu[:, :f], gu[:, f:]
-            sg = torch.sigmoid(g.float())
-            dg = dact.float() * u.float() * (sg * (1 + g.float() * (1 - sg)))
-            return torch.cat([dg.to(gu.dtype), dact * torch.nn.functional.silu(g)], 1)
-        dact = _grad(dact)
+        rows, f = dact.shape
+        grads = _grads((gu, s), dact) if gu.shape == (rows, 2 * f) and s.shape == dact.shape else None
+        if grads is None:
+            return _torch_grad(lambda t: _swiglu_torch(t, f), gu, dact)
+        (dact,) = grads
         dgu = torch.empty_like(gu)
         _call("compact_block_swiglu_bwd", gu.data_ptr(), s.data_ptr(), dact.data_ptr(), dgu.data_ptr(), rows, f,
               _stream(gu))
         return dgu
 
 
+def _swiglu_torch(gu, f):
+    return torch.nn.functional.silu(gu[:, :f]) * gu[:, f:]
+
+
 def swiglu(gu, f):
     """silu(gu[:, :f]) * gu[:, f:]."""
     if gu.dim() == 2 and gu.shape[1] == 2 * f and f % 8 == 0 and usable(gu):
         return _SwigluFn.apply(gu)
-    return torch.nn.functional.silu(gu[:, :f]) * gu[:, f:]
+    return _swiglu_torch(gu, f)
 
 
 # ------------------------- uncompressed layers -------------------------------
@@ -232,7 +263,7 @@ class _DenseFn(torch.autograd.Function):
         dx = dy @ W.t() if ctx.needs_input_grad[0] else None
         if not ctx.needs_input_grad[1]:
             return dx, None
-        if torch.is_grad_enabled() or not usable(x, dy):
+        if torch.is_grad_enabled() or not usable(x, dy) or x.dim() != 2 or x.shape[0] != dy.shape[0]:
             return dx, x.t() @ dy
         T, n = x.shape
         m = dy.shape[1]
@@ -306,18 +337,18 @@ class _CrossEntropyFn(torch.autograd.Function):
         _call("compact_block_ce_fwd",
               ctypes.byref(_CeArgs(logits.data_ptr(), targets.data_ptr(), lse.data_ptr(), loss_row.data_ptr(),
                                    loss.data_ptr(), lse.data_ptr() + 4 * rows, rows, V, IGNORE)), _stream(logits))
+        ctx.size = rows, V
         ctx.save_for_backward(logits, targets, lse)
         return loss
 
     @staticmethod
     def backward(ctx, dloss):
         logits, targets, lse = ctx.saved_tensors
-        rows, V = logits.shape
-        if torch.is_grad_enabled():
-            keep = targets != IGNORE
-            p = torch.softmax(logits.float(), -1)
-            p = p - torch.nn.functional.one_hot(targets.clamp(min=0), V)
-            return (p * (keep.float() * dloss / lse[rows]).unsqueeze(-1)).to(logits.dtype), None
+        rows, V = ctx.size
+        if (torch.is_grad_enabled() or not _plain(dloss) or not usable(logits) or logits.shape != (rows, V)
+                or not _companion(lse, logits, torch.float32, (rows + 1,))
+                or not _companion(targets, logits, torch.int64, (rows,))):
+            return _torch_grad(lambda t: _cross_entropy_torch(t, targets), logits, dloss), None
         dloss = dloss.float().contiguous()
         dx = torch.empty_like(logits)
         _call("compact_block_ce_bwd",
@@ -326,9 +357,13 @@ class _CrossEntropyFn(torch.autograd.Function):
         return dx, None
 
 
+def _cross_entropy_torch(logits, targets):
+    return torch.nn.functional.cross_entropy(logits.float(), targets)
+
+
 def cross_entropy(logits, targets):
     """F.cross_entropy(logits.float(), targets) for 2-D logits and class targets."""
     if (logits.dim() == 2 and _plain(targets) and targets.dtype == torch.int64 and targets.dim() == 1
             and targets.shape[0] == logits.shape[0] < MAX_ROWS and targets.device == logits.device and usable(logits)):
         return _CrossEntropyFn.apply(logits, targets.contiguous())
-    return torch.nn.functional.cross_entropy(logits.float(), targets)
+    return _cross_entropy_torch(logits, targets)

@@ -190,3 +190,31 @@ def test_routes_that_stay_torch():
     loss = ops.cross_entropy(z, torch.tensor([40, 1], device=dev()))
     loss.backward()
     assert torch.isnan(loss) and torch.isnan(z.grad[0]).all()
+
+
+def _calls():
+    norm, x, gu, z = blk.RMSNorm(64), _rand(10, 64), _rand(10, 48, scale=2.0), _rand(10, 40)
+    t = torch.arange(10, device=dev())
+    return [(norm, x), (lambda v: ops.swiglu(v, 24), gu), (lambda v: ops.cross_entropy(v, t), z)]
+
+
+@pytest.mark.parametrize("i", range(3))
+def test_saved_tensors_from_hooks_and_batched_gradients(i):
+    """What a hook gives back in another type or layout, and batched gradients, take the
+    torch expressions; offloading to the host and back keeps the kernels, bit for bit."""
+    fn, x = _calls()[i]
+    x.requires_grad_(True)
+    out = fn(x)
+    dy = (0.5 + torch.rand_like(out.float())).to(out.dtype)
+    (want,) = torch.autograd.grad(out, x, dy, retain_graph=True)
+    with torch.autograd.graph.save_on_cpu():
+        off = fn(x)
+    assert torch.equal(torch.autograd.grad(off, x, dy)[0], want)
+    for pack in (lambda v: v.float() if v.is_floating_point() else v, lambda v: v.t().contiguous().t() if v.dim() == 2 else v):
+        with torch.autograd.graph.saved_tensors_hooks(pack, lambda v: v):
+            y = fn(x)
+        g = torch.autograd.grad(y, x, dy)[0].double()
+        assert (g - want.double()).norm() <= 8 * BF16_U * want.double().norm()
+    (b,) = torch.autograd.grad(out, x, torch.stack([dy, 2 * dy]), is_grads_batched=True)
+    assert (b[0].double() - want.double()).norm() <= 8 * BF16_U * want.double().norm()
+    assert (b[1].double() - 2 * want.double()).norm() <= 16 * BF16_U * want.double().norm()
