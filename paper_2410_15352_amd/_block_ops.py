@@ -136,7 +136,9 @@ def _torch_grad(fn, x, dy):
 
 # ------------------------------- RMSNorm -----------------------------------
 
-def rmsnorm_reference_grad(x, rstd, g, dy):
+def rmsnorm_reference_grad(x, rstd, g, dy, eps):
+    if torch.is_grad_enabled():  # recorded: the saved 1 / rms is a constant, its own derivative is needed too
+        rstd = torch.rsqrt(x.float().square().mean(-1) + eps)
     xhat = x.float() * rstd.unsqueeze(-1)
     dyf = dy.float()
     gdy = dyf * g.float()
@@ -162,7 +164,7 @@ class _NormFn(torch.autograd.Function):
                                      None if add is None else total.data_ptr(), y.data_ptr(), rstd.data_ptr(), rows, d,
                                      eps)), _stream(x))
         ctx.set_materialize_grads(False)
-        ctx.added = add is not None
+        ctx.added, ctx.eps = add is not None, eps
         ctx.save_for_backward(x if add is None else total, rstd, g)
         return (x if add is None else total), y
 
@@ -175,7 +177,7 @@ class _NormFn(torch.autograd.Function):
         if x.shape == dy.shape and g.shape == dy.shape[-1:] and _companion(rstd, x, torch.float32, dy.shape[:-1]):
             grads = _grads((x, g), dy, dres)
         if grads is None:
-            dx, dg = rmsnorm_reference_grad(x, rstd, g, dy)
+            dx, dg = rmsnorm_reference_grad(x, rstd, g, dy, ctx.eps)
             dx = dx if dres is None else dx + dres
             return dx, dx if ctx.added else None, dg, None
         dy, dres = grads

@@ -41,12 +41,13 @@ class _RMSNormFn(torch.autograd.Function):
         xf = x.float()
         rstd = torch.rsqrt(xf.square().mean(-1) + eps)
         ctx.save_for_backward(x, rstd, g)
+        ctx.eps = eps
         return (xf * rstd.unsqueeze(-1) * g.float()).to(x.dtype)
 
     @staticmethod
     def backward(ctx, dy):
         x, rstd, g = ctx.saved_tensors
-        dx, dg = ops.rmsnorm_reference_grad(x, rstd, g, dy)
+        dx, dg = ops.rmsnorm_reference_grad(x, rstd, g, dy, ctx.eps)
         return dx, dg, None
 
 
