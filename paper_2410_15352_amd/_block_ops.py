@@ -70,7 +70,11 @@ def _stream(t):
 
 
 def _plain(t):
-    return type(t) in (torch.Tensor, torch.nn.Parameter)
+    """A tensor of its own storage: no subclass, no functorch wrapper, none of the batched
+    tensors that is_grads_batched hands to a backward (in the engine's thread, where no
+    functorch level is seen)."""
+    return (type(t) in (torch.Tensor, torch.nn.Parameter) and not torch._C._functorch.is_functorch_wrapped_tensor(t)
+            and not torch._C._functorch.is_legacy_batchedtensor(t))
 
 
 def usable(*tensors):

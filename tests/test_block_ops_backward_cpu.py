@@ -88,6 +88,27 @@ def test_batched_gradients(no_gpu, fn):
     assert own.shape == (3, 6, 32) and (own.double() - want.double()).norm() <= 4 * BF16_U * want.double().norm()
 
 
+def test_wrapped_tensors_are_not_plain():
+    """Tensors without a storage of their own are known by themselves, whatever the thread."""
+    seen = []
+
+    class Look(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, x):
+            return x * 1
+
+        @staticmethod
+        def backward(ctx, dy):
+            seen.append(ops._plain(dy))
+            return dy
+
+    x = torch.randn(3, requires_grad=True)
+    torch.autograd.grad(Look.apply(x), x, torch.randn(2, 3), is_grads_batched=True)
+    torch.func.vmap(lambda v: (seen.append(ops._plain(v)), v)[1])(torch.randn(2, 3))
+    torch.func.grad(lambda v: (seen.append(ops._plain(v)), v.sum())[1])(torch.randn(3))
+    assert seen == [False] * 3 and ops._plain(x) and ops._plain(torch.nn.Parameter(x.detach()))
+
+
 @pytest.mark.parametrize("hook", list(HOOKS))
 def test_norm_with_residual_and_saved_tensors_from_hooks(no_gpu, hook):
     """Both results used: the gradients of x and of its norm meet."""
