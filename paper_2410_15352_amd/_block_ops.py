@@ -31,8 +31,8 @@ class _NormGradArgs(ctypes.Structure):
 
 
 class _CeArgs(ctypes.Structure):
-    _fields_ = [("x", _vp), ("target", _vp), ("lse", _vp), ("loss_row", _vp), ("loss", _vp), ("count", _vp), ("rows", _i64),
-                ("V", _i64), ("ignore_index", _i64)]
+    _fields_ = [("x", _vp), ("target", _vp), ("lse", _vp), ("loss_row", _vp), ("loss", _vp), ("count", _vp), ("valid", _vp),
+                ("rows", _i64), ("V", _i64), ("ignore_index", _i64)]
 
 
 class _CeGradArgs(ctypes.Structure):
@@ -340,9 +340,14 @@ class _CrossEntropyFn(torch.autograd.Function):
         lse = torch.empty(rows + 1, dtype=torch.float32, device=logits.device)  # and the count
         loss_row = torch.empty(rows, dtype=torch.float32, device=logits.device)
         loss = torch.empty((), dtype=torch.float32, device=logits.device)
+        valid = torch.empty((), dtype=torch.float32, device=logits.device)
         _call("compact_block_ce_fwd",
               ctypes.byref(_CeArgs(logits.data_ptr(), targets.data_ptr(), lse.data_ptr(), loss_row.data_ptr(),
-                                   loss.data_ptr(), lse.data_ptr() + 4 * rows, rows, V, IGNORE)), _stream(logits))
+                                   loss.data_ptr(), lse.data_ptr() + 4 * rows, valid.data_ptr(), rows, V, IGNORE)),
+              _stream(logits))
+        # on the GPU, as torch's own cross-entropy checks its targets; where that check
+        # is compiled out, the loss and the row's gradient are NaN
+        torch._assert_async(valid, "cross_entropy: a target is neither a class nor ignore_index")
         ctx.size = rows, V
         ctx.save_for_backward(logits, targets, lse)
         return loss

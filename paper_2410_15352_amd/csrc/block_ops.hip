@@ -354,18 +354,22 @@ __global__ __launch_bounds__(256) void k_ce_fwd(CeArgs a) {
   }
 }
 
-// The mean of the rows' losses over the targets that count, and their number; one workgroup, fp64 sums in a fixed order.
+// The mean of the rows' losses over the targets that count, their number, and whether
+// every target is valid; one workgroup, fp64 sums in a fixed order.
 __global__ __launch_bounds__(1024) void k_ce_mean(CeArgs a) {
   __shared__ double sl[1024], sc[1024];
   double l = 0.0, c = 0.0;
+  int bad = 0;
   for (int64_t r = threadIdx.x; r < a.rows; r += 1024) {
-    if (a.target[r] == a.ignore_index) continue;
+    const int64_t t = a.target[r];
+    if (t == a.ignore_index) continue;
+    bad |= t < 0 || t >= a.V ? 1 : 0;
     l += a.loss_row[r];
     c += 1.0;
   }
   sl[threadIdx.x] = l;
   sc[threadIdx.x] = c;
-  __syncthreads();
+  bad = __syncthreads_or(bad);
   for (int d = 512; d > 0; d >>= 1) {
     if (static_cast<int>(threadIdx.x) < d) {
       sl[threadIdx.x] += sl[threadIdx.x + d];
@@ -376,22 +380,24 @@ __global__ __launch_bounds__(1024) void k_ce_mean(CeArgs a) {
   if (threadIdx.x == 0) {
     a.loss[0] = static_cast<float>(sl[0] / sc[0]);
     a.count[0] = static_cast<float>(sc[0]);
+    a.valid[0] = bad != 0 ? 0.0f : 1.0f;
   }
 }
 
-// dx = (softmax(x) - onehot(target)) dloss / count; zero for ignored rows, NaN (as
-// the loss) for a target outside 0 .. V - 1.
+// dx = (softmax(x) - onehot(target)) dloss / count; softmax(x) times zero for ignored
+// rows (NaN where that is), NaN (as the loss) for a target outside 0 .. V - 1.
 __global__ __launch_bounds__(256) void k_ce_bwd(CeGradArgs a) {
   const int64_t row = blockIdx.x, begin = row * a.V, end = begin + a.V, total = a.rows * a.V;
   const int64_t t = a.target[row];
   const bool ignored = t == a.ignore_index;
-  const float lse = t >= 0 && t < a.V ? a.lse[row] : __builtin_nanf(""), scale = ignored ? 0.0f : a.dloss[0] / a.count[0];
+  const float lse = ignored || (t >= 0 && t < a.V) ? a.lse[row] : __builtin_nanf("");
+  const float scale = ignored ? 0.0f : a.dloss[0] / a.count[0];
   for (int64_t q = begin / 8 + threadIdx.x; q * 8 < end; q += 256) {
     Chunk c = ce_chunk(a.x, q, begin, end, total);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float p = ce_exp(c.v[e] - lse) - (q * 8 + e == begin + t ? 1.0f : 0.0f);
-      c.v[e] = ignored ? 0.0f : p * scale;
+      c.v[e] = p * scale;
     }
     if (c.lo == 0 && c.hi == 8) {
       reinterpret_cast<u32x4*>(a.dx)[q] = pack8(c.v);

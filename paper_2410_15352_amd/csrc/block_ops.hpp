@@ -43,6 +43,7 @@ struct CeArgs {
   float* loss_row;        // [rows] scratch
   float* loss;            // the mean
   float* count;           // number of targets that count
+  float* valid;           // 1 if every target is ignore_index or in 0 .. V - 1, else 0
   int64_t rows, V, ignore_index;
 };
 

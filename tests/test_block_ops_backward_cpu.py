@@ -37,6 +37,7 @@ def _fake_call(name, *args):
 def no_gpu(monkeypatch):
     monkeypatch.setattr(ops, "_call", _fake_call)
     monkeypatch.setattr(ops, "_stream", lambda t: 0)
+    monkeypatch.setattr(torch, "_assert_async", lambda t, msg: None)
 
 
 def _bf16(*shape, seed=0, scale=1.0):
@@ -174,3 +175,11 @@ def test_second_derivatives_of_the_block_kernels(no_gpu):
     _close(_second(lambda v: [ops._CrossEntropyFn.apply(v, t)], [z], [torch.tensor(2.0)], [_bf16(6, 32, seed=9)]),
            _double(lambda v: [torch.nn.functional.cross_entropy(v, t)], [z], [torch.tensor(2.0)],
                    [_bf16(6, 32, seed=9)]), 4 * BF16_U)
+
+
+def test_cross_entropy_asserts_that_its_targets_are_classes(no_gpu, monkeypatch):
+    """Every forward checks its targets on the device, without waiting for it."""
+    seen = []
+    monkeypatch.setattr(torch, "_assert_async", lambda t, msg: seen.append((t.numel(), msg)))
+    ops._CrossEntropyFn.apply(_bf16(3, 32), torch.tensor([0, 32, 1]))
+    assert [n for n, _ in seen] == [1]

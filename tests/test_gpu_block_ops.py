@@ -193,11 +193,38 @@ def test_routes_that_stay_torch():
     x = _rand(4096, 64).requires_grad_(True)
     with torch.autocast("cuda", dtype=torch.float16):
         assert not ops.usable(x) and ops.dense(x, W).dtype == torch.float16
-    # a target that is no class: NaN in the loss and in its row's gradient
-    z = _rand(2, 40).requires_grad_(True)
-    loss = ops.cross_entropy(z, torch.tensor([40, 1], device=dev()))
+
+
+@pytest.mark.parametrize("bad", [-1, 40, 1 << 40, None])
+def test_cross_entropy_checks_its_targets(monkeypatch, bad):
+    """The flag that the forward's assertion looks at (the assertion itself ends the
+    process, so it is left out here); behind it the loss and the row's gradient are NaN."""
+    seen = []
+    monkeypatch.setattr(torch, "_assert_async", lambda t, msg: seen.append(t))
+    t = torch.arange(1500, device=dev()) % 40
+    t[7] = ops.IGNORE
+    if bad is not None:
+        t[1200] = bad
+    z = _rand(1500, 40).requires_grad_(True)
+    loss = ops.cross_entropy(z, t)
     loss.backward()
-    assert torch.isnan(loss) and torch.isnan(z.grad[0]).all()
+    assert [v.item() for v in seen] == [1.0 if bad is None else 0.0]
+    nan = torch.isnan(z.grad).any(1)
+    assert bool(torch.isnan(loss)) == (bad is not None) and nan[1200] == (bad is not None) and nan.sum() <= 1
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+def test_cross_entropy_ignored_row_that_is_not_finite(value):
+    """NaN where torch's gradient is NaN, zero elsewhere in the row, the other rows as usual."""
+    t = torch.tensor([3, ops.IGNORE, 5, ops.IGNORE], device=dev())
+    x = _rand(4, 41)
+    x[1, 7] = value
+    x[3] = value if value == float("-inf") else x[3]
+    x.requires_grad_(True)
+    (g,) = torch.autograd.grad(ops.cross_entropy(x, t), x)
+    (w,) = torch.autograd.grad(torch.nn.functional.cross_entropy(x.float(), t), x)
+    assert torch.equal(torch.isnan(g), torch.isnan(w)) and not torch.nan_to_num(g)[1::2].any()
+    _close(g[0::2], w[0::2].double(), extra=2 * BF16_U)
 
 
 def _calls():
