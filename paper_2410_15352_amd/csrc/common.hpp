@@ -64,8 +64,9 @@ __device__ __forceinline__ int batch_layer_of(const int* begin, int count, int b
 __host__ __device__ constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 __host__ __device__ constexpr int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
-// Layer tables of Alg. 3's launches: sizes once per distinct shape.
+// Layer tables of Alg. 3's launches, by shape: sizes once per distinct shape.
 constexpr int kStepShapes = 8;  // distinct shapes per launch
+constexpr int kStepFew = 8;     // layers of the small table: a launch of few has 0.5 KB of arguments, not 4
 
 struct StepShape {
   int n, m, r, ldw;

@@ -1133,8 +1133,9 @@ void plan_step(void* W, int64_t ldw, const float* G, float* M, float* V, int64_t
 }
 
 // The layers of one launch's table: as many of plans[i0 ..] as hold at most
-// `max_layers` layers, kStepShapes distinct shapes and 2^30 workgroups.  Fills
-// the table's shapes and each layer's shape index (zero on entry).
+// `max_layers` layers and 2^30 workgroups, and where shapes are kept once
+// (shape != nullptr) kStepShapes distinct ones: fills the table's shapes and each
+// layer's shape index (zero on entry).
 int64_t take_layers(const std::vector<StepPlan>& plans, int64_t i0, int64_t max_layers, bool adam,
                     StepShape* shape, uint32_t* shape_of) {
   int shapes = 0;
@@ -1144,6 +1145,7 @@ int64_t take_layers(const std::vector<StepPlan>& plans, int64_t i0, int64_t max_
     const StepPlan& P = plans[i0 + k];
     blocks += adam ? P.adam_blocks + P.pt_blocks : P.dec_tiles;
     if (k > 0 && blocks > int64_t(1) << 30) break;
+    if (shape == nullptr) continue;
     int f = 0;
     while (f < shapes && (shape[f].n != P.shape.n || shape[f].m != P.shape.m || shape[f].r != P.shape.r ||
                           shape[f].ldw != P.shape.ldw))
@@ -1160,48 +1162,103 @@ int64_t take_layers(const std::vector<StepPlan>& plans, int64_t i0, int64_t max_
 // Layers per launch so that `count` layers make equal launches of at most `most`.
 int64_t even_share(int64_t count, int64_t most) { return ceil_div(count, ceil_div(count, most)); }
 
+// The layers of the next launch over plans[i0 ..], and whether its table is the one
+// by shape (`batch`, filled as above): that one only where it takes more layers than
+// the one with each layer's own sizes.  (One layer of 1024 x 1024: 14.9 us by shape, 13.3
+// with its own sizes and the small table, 14.5 with 40 whole layers in the table.)
+template <class Batch>
+int64_t next_launch(const std::vector<StepPlan>& plans, int64_t i0, int64_t most_batch, int64_t most_own, bool adam,
+                    Batch& batch, bool& by_shape) {
+  const int64_t left = static_cast<int64_t>(plans.size()) - i0;
+  const int64_t own = take_layers(plans, i0, even_share(left, most_own), adam, nullptr, nullptr);
+  by_shape = false;
+  if (own == left) return own;
+  const int64_t k = take_layers(plans, i0, even_share(left, most_batch), adam, batch.shape, batch.shape_of);
+  by_shape = k > own;
+  return by_shape ? k : own;
+}
+
+template <class Table>
+int launch_adam(Table& b, const StepPlan* P, int64_t k, const AdamConsts& c, void* ws, hipStream_t s) {
+  b.c = c;
+  b.ws = static_cast<char*>(ws);
+  b.count = static_cast<int>(k);
+  int64_t ab = 0, pb = 0;
+  for (int64_t j = 0; j < k; ++j) {
+    ab += P[j].adam_blocks;
+    pb += P[j].pt_blocks;
+    b.adam_begin[j + 1] = static_cast<int>(ab);
+    b.pt_begin[j + 1] = static_cast<int>(pb);
+  }
+  hipLaunchKernelGGL(k_adam_pt_batched<Table>, dim3(static_cast<uint32_t>(ab + pb)), dim3(256), 0, s, b);
+  return check_launch("Adam and P^T staging");
+}
+
+template <int N>
+int launch_adam_own(const StepPlan* P, int64_t k, const AdamConsts& c, void* ws, hipStream_t s) {
+  StepOwn<N> o{};
+  for (int64_t j = 0; j < k; ++j)
+    o.layer[j] = StepOwnLayer{P[j].G, P[j].M, P[j].V, P[j].key, P[j].shape.n, P[j].shape.m, P[j].shape.r,
+                              static_cast<uint32_t>(P[j].offset / kWsAlign)};
+  return launch_adam(o, P, k, c, ws, s);
+}
+
+template <class Table>
+int launch_dec(Table& d, const StepPlan* P, int64_t k, int w_dtype, void* ws, hipStream_t s) {
+  d.ws = static_cast<char*>(ws);
+  d.count = static_cast<int>(k);
+  for (int64_t j = 0; j < k; ++j) d.begin[j + 1] = d.begin[j] + static_cast<int>(P[j].dec_tiles);
+  const hipError_t e = dec_w4_launch(d, w_dtype == COMPACT_F32, s);
+  if (e != hipSuccess) return fail(COMPACT_EHIP, "decompression launch: %s", hipGetErrorString(e));
+  return COMPACT_OK;
+}
+
+template <int N>
+int launch_dec_own(const StepPlan* P, int64_t k, int w_dtype, void* ws, hipStream_t s) {
+  DecW4Own<N> o{};
+  for (int64_t j = 0; j < k; ++j)
+    o.layer[j] = DecOwnLayer{P[j].W, static_cast<uint32_t>(P[j].offset / kWsAlign), P[j].coef, P[j].shape};
+  return launch_dec(o, P, k, w_dtype, ws, s);
+}
+
 // Adam (+ P^T staging) for every layer of `plans`, then the decompression, in as
 // few launches as the layer tables allow.
 int launch_steps(const std::vector<StepPlan>& plans, const AdamConsts& c, int dtype, int w_dtype, void* ws,
                  hipStream_t s) {
   int st;
   const int64_t count = static_cast<int64_t>(plans.size());
-  for (int64_t i0 = 0; i0 < count;) {
+  bool by_shape = false;
+  for (int64_t i0 = 0, k; i0 < count; i0 += k) {
     StepBatch b{};
-    b.c = c;
-    b.ws = static_cast<char*>(ws);
-    const int64_t k = take_layers(plans, i0, even_share(count, kStepBatch), true, b.shape, b.shape_of);
-    b.count = static_cast<int>(k);
-    int64_t ab = 0, pb = 0;
-    for (int64_t j = 0; j < k; ++j) {
-      const StepPlan& P = plans[i0 + j];
-      b.G[j] = P.G; b.M[j] = P.M; b.V[j] = P.V; b.key[j] = P.key;
-      b.base[j] = static_cast<uint32_t>(P.offset / kWsAlign);
-      ab += P.adam_blocks;
-      pb += P.pt_blocks;
-      b.adam_begin[j + 1] = static_cast<int>(ab);
-      b.pt_begin[j + 1] = static_cast<int>(pb);
+    k = next_launch(plans, i0, kStepBatch, kStepOwn, true, b, by_shape);
+    const StepPlan* P = &plans[i0];
+    if (by_shape) {
+      for (int64_t j = 0; j < k; ++j) {
+        b.G[j] = P[j].G; b.M[j] = P[j].M; b.V[j] = P[j].V; b.key[j] = P[j].key;
+        b.base[j] = static_cast<uint32_t>(P[j].offset / kWsAlign);
+      }
+      if ((st = launch_adam(b, P, k, c, ws, s))) return st;
+    } else if ((st = k <= kStepFew ? launch_adam_own<kStepFew>(P, k, c, ws, s)
+                                   : launch_adam_own<kStepOwn>(P, k, c, ws, s))) {
+      return st;
     }
-    hipLaunchKernelGGL(k_adam_pt_batched, dim3(static_cast<uint32_t>(ab + pb)), dim3(256), 0, s, b);
-    if ((st = check_launch("Adam and P^T staging"))) return st;
-    i0 += k;
   }
   if (dtype != COMPACT_BF16) return COMPACT_OK;
-  for (int64_t i0 = 0; i0 < count;) {
+  for (int64_t i0 = 0, k; i0 < count; i0 += k) {
     DecW4Batch d{};
-    d.ws = static_cast<char*>(ws);
-    const int64_t k = take_layers(plans, i0, even_share(count, kDecBatch), false, d.shape, d.shape_of);
-    d.count = static_cast<int>(k);
-    for (int64_t j = 0; j < k; ++j) {
-      const StepPlan& P = plans[i0 + j];
-      d.W[j] = P.W;
-      d.base[j] = static_cast<uint32_t>(P.offset / kWsAlign);
-      d.coef[j] = P.coef;
-      d.begin[j + 1] = d.begin[j] + static_cast<int>(P.dec_tiles);
+    k = next_launch(plans, i0, kDecBatch, kDecOwn, false, d, by_shape);
+    const StepPlan* P = &plans[i0];
+    if (by_shape) {
+      for (int64_t j = 0; j < k; ++j) {
+        d.W[j] = P[j].W;
+        d.base[j] = static_cast<uint32_t>(P[j].offset / kWsAlign);
+        d.coef[j] = P[j].coef;
+      }
+      if ((st = launch_dec(d, P, k, w_dtype, ws, s))) return st;
+    } else if ((st = k <= kStepFew ? launch_dec_own<kStepFew>(P, k, w_dtype, ws, s)
+                                   : launch_dec_own<kDecOwn>(P, k, w_dtype, ws, s))) {
+      return st;
     }
-    const hipError_t e = dec_w4_launch(d, w_dtype == COMPACT_F32, s);
-    if (e != hipSuccess) return fail(COMPACT_EHIP, "decompression launch: %s", hipGetErrorString(e));
-    i0 += k;
   }
   return COMPACT_OK;
 }

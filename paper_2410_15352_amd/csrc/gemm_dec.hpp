@@ -42,7 +42,7 @@ constexpr int kDecAhead = kDecStages - 1;             // K steps copied ahead
 constexpr uint32_t kDecStage = kDecK * kDecT * 2;     // 4 KB, one operand
 constexpr uint32_t kDecBBase = kDecStages * kDecStage;
 constexpr size_t kDecLds = 2u * kDecStages * kDecStage;  // 32 KB
-constexpr int kDecBatch = 180;                        // layers per launch
+constexpr int kDecBatch = 180, kDecOwn = 112;          // layers per launch (DecW4Batch, DecW4Own)
 
 struct DecW4Layer {
   void* W;              // [n x m], ld ldw; bf16 or fp32 (the launch's w_f32)
@@ -66,18 +66,43 @@ struct DecW4Batch {
 };
 static_assert(sizeof(DecW4Batch) <= 4096, "kernel argument size");
 
-__device__ __forceinline__ DecW4Layer dec_layer(const DecW4Batch& d, int l) {
-  const StepShape& sh = d.shape[shape_index(d.shape_of, l)];
-  const char* base = d.ws + int64_t(256) * d.base[l];
+// The same with each layer's own sizes (kernels_common.hpp, StepOwn).
+struct DecOwnLayer {
+  void* W;
+  uint32_t base;
+  float coef;
+  StepShape shape;
+};
+
+template <int N>
+struct DecW4Own {
+  int count;
+  char* ws;
+  DecOwnLayer layer[N];
+  int begin[N + 1];
+};
+static_assert(sizeof(DecW4Own<kDecOwn>) <= 4096, "kernel argument size");
+
+__device__ __forceinline__ DecW4Layer dec_layer_of(void* W, const char* base, float coef, const StepShape& sh) {
   DecW4Layer p;
-  p.W = d.W[l];
+  p.W = W;
   p.N = reinterpret_cast<const uint16_t*>(base);
   p.pt = reinterpret_cast<const uint16_t*>(base + step_n_bytes(sh.m, sh.r, 2));
   p.ldw = sh.ldw; p.ldn = static_cast<int>(step_ldn(sh.m)); p.ldpt = static_cast<int>(step_ldpt(sh.n));
   p.n = sh.n; p.m = sh.m; p.r = sh.r;
   p.tiles_c = (sh.m + kDecT - 1) / kDecT;
-  p.coef = d.coef[l];
+  p.coef = coef;
   return p;
+}
+
+__device__ __forceinline__ DecW4Layer dec_layer(const DecW4Batch& d, int l) {
+  return dec_layer_of(d.W[l], d.ws + int64_t(256) * d.base[l], d.coef[l], d.shape[shape_index(d.shape_of, l)]);
+}
+
+template <int N>
+__device__ __forceinline__ DecW4Layer dec_layer(const DecW4Own<N>& d, int l) {
+  const DecOwnLayer& L = d.layer[l];
+  return dec_layer_of(L.W, d.ws + int64_t(256) * L.base, L.coef, L.shape);
 }
 
 // s_waitcnt vmcnt(N) lgkmcnt(0), then s_barrier.

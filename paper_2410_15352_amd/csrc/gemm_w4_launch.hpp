@@ -34,6 +34,7 @@ bool dec_w4_eligible(int64_t n, int64_t m, int64_t r, int64_t ldw, int64_t ldn, 
 
 // W <- W - coef P N for every layer of the batch: one workgroup per 128 x 128
 // tile of W (begin[] holds each layer's first workgroup).
-hipError_t dec_w4_launch(const DecW4Batch& d, bool w_f32, hipStream_t stream);
+template <class Table>  // DecW4Batch or DecW4Own<N>
+hipError_t dec_w4_launch(const Table& d, bool w_f32, hipStream_t stream);
 
 }  // namespace compact

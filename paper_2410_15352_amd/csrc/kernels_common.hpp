@@ -42,13 +42,18 @@ struct AdamLayer {
 };
 
 // Layers per launch.  A launch's first and last wave of workgroups leave CUs idle
-// for some microseconds, so the fewer launches the better, and a layer table in the
-// kernel's arguments (4096 bytes) holds what cannot be derived only: pointers, the
-// key, the offset of the layer's scratch, and sizes once per distinct shape.  (The
-// 168 layers of LLaMA-350M: five Adam launches of 43 us and five decompression
-// launches of 78 us with 40 layers each; two and one launch, the whole step 603 ->
-// 548 us.)
+// for some microseconds, so the fewer launches the better.  The kernel's arguments
+// (4096 bytes) hold one of two tables:
+//   StepOwn    the layers one by one, each with its sizes: any shapes, and one
+//              scalar load less at the head of every workgroup
+//   StepBatch  what cannot be derived only (pointers, the key, the offset of the
+//              layer's scratch) and sizes once per distinct shape
+// (The 168 layers of LLaMA-350M: five Adam launches of 43 us and five decompression
+// launches of 78 us with 40 layers each; two and one launch by shape, the whole step
+// 603 -> 548 us.  168 layers of 1024 x 1024 with 9 and more shapes among them, 8 shapes
+// a launch: 541 us; with their own sizes, 3 + 2 launches: 304, and 361 with 40 a launch.)
 constexpr int kStepBatch = 84;
+constexpr int kStepOwn = 70;
 constexpr int kAdamVec = 4;     // float4 groups per thread
 
 struct StepBatch {
@@ -66,6 +71,52 @@ struct StepBatch {
   uint32_t shape_of[(kStepBatch + 3) / 4];  // shape_index
 };
 static_assert(sizeof(StepBatch) <= 4096, "kernel argument size");
+
+struct StepOwnLayer {
+  const float* G;
+  float* M;
+  float* V;
+  PhiloxKey key;
+  int n, m, r;
+  uint32_t base;
+};
+
+template <int N>
+struct StepOwn {
+  AdamConsts c;
+  int count;
+  char* ws;
+  StepOwnLayer layer[N];
+  int adam_begin[N + 1];
+  int pt_begin[N + 1];
+};
+static_assert(sizeof(StepOwn<kStepOwn>) <= 4096, "kernel argument size");
+
+__device__ __forceinline__ AdamLayer adam_layer(const AdamConsts& c, char* base, int n, int m, int r) {
+  AdamLayer p;
+  p.N = base;
+  p.pt = reinterpret_cast<uint16_t*>(base + step_n_bytes(m, r, c.n_f32 ? 4 : 2));
+  p.ldn = static_cast<int>(step_ldn(m)); p.r = r; p.m = m;
+  p.ldpt = static_cast<int>(step_ldpt(n)); p.n = n;
+  return p;
+}
+
+__device__ __forceinline__ AdamLayer step_layer(const StepBatch& s, int l) {
+  const StepShape& sh = s.shape[shape_index(s.shape_of, l)];
+  AdamLayer p = adam_layer(s.c, s.ws + int64_t(256) * s.base[l], sh.n, sh.m, sh.r);
+  p.G = s.G[l]; p.M = s.M[l]; p.V = s.V[l];
+  p.key = s.key[l];
+  return p;
+}
+
+template <int N>
+__device__ __forceinline__ AdamLayer step_layer(const StepOwn<N>& s, int l) {
+  const StepOwnLayer& L = s.layer[l];
+  AdamLayer p = adam_layer(s.c, s.ws + int64_t(256) * L.base, L.n, L.m, L.r);
+  p.G = L.G; p.M = L.M; p.V = L.V;
+  p.key = L.key;
+  return p;
+}
 
 __device__ __forceinline__ void adam_one(const AdamConsts& c, float g, float mo, float vo, float& m1, float& v1,
                                          float& nv) {
@@ -212,7 +263,8 @@ __host__ __device__ inline int pt_blocks(int kind, int64_t r, int64_t ldpt) {
   return static_cast<int>(ceil_div(proj_t_units(kind, r, ldpt), 256));
 }
 
-__global__ void k_adam_pt_batched(StepBatch s) {
+template <class Table>
+__global__ void k_adam_pt_batched(Table s) {
   const int na = s.adam_begin[s.count], np = s.pt_begin[s.count];
   const int64_t total = static_cast<int64_t>(na) + np;
   const int64_t b = blockIdx.x;
@@ -222,15 +274,7 @@ __global__ void k_adam_pt_batched(StepBatch s) {
   const bool adam = static_cast<int>((b + 1) * na / total) > before;
   const int idx = adam ? before : static_cast<int>(b) - before;
   const int l = batch_layer_of(adam ? s.adam_begin : s.pt_begin, s.count, idx);
-  const StepShape& sh = s.shape[shape_index(s.shape_of, l)];
-  AdamLayer p;
-  p.G = s.G[l]; p.M = s.M[l]; p.V = s.V[l];
-  char* base = s.ws + int64_t(256) * s.base[l];
-  p.N = base;
-  p.pt = reinterpret_cast<uint16_t*>(base + step_n_bytes(sh.m, sh.r, s.c.n_f32 ? 4 : 2));
-  p.key = s.key[l];
-  p.ldn = static_cast<int>(step_ldn(sh.m)); p.r = sh.r; p.m = sh.m;
-  p.ldpt = static_cast<int>(step_ldpt(sh.n)); p.n = sh.n;
+  const AdamLayer p = step_layer(s, l);
   if (adam) {
     const int nb = s.adam_begin[l + 1] - s.adam_begin[l];
     adam_range(p, s.c, static_cast<int64_t>(idx - s.adam_begin[l]) * blockDim.x + threadIdx.x,

@@ -26,8 +26,8 @@ __global__ __launch_bounds__(256, 1) void k_ghat_w4(GhatW4Params p) {
 __global__ __launch_bounds__(256, 1) void k_ghat_direct(GhatDirectParams p) { ghat_direct(p); }
 
 // Four workgroups per CU for bf16 W (at most 128 registers per lane), two for fp32 W.
-template <bool WF32>
-__global__ __launch_bounds__(256, WF32 ? 2 : 4) void k_dec_w4(DecW4Batch d) {
+template <bool WF32, class Table>
+__global__ __launch_bounds__(256, WF32 ? 2 : 4) void k_dec_w4(Table d) {
   const int b = static_cast<int>(xcd_remap(blockIdx.x, gridDim.x));
   const int l = batch_layer_of(d.begin, d.count, b);
   dec_w4_tile<WF32>(dec_layer(d, l), b - d.begin[l]);
@@ -129,15 +129,20 @@ bool dec_w4_eligible(int64_t n, int64_t m, int64_t r, int64_t ldw, int64_t ldn, 
   return n < lim && m < lim;
 }
 
-hipError_t dec_w4_launch(const DecW4Batch& d, bool w_f32, hipStream_t stream) {
+template <class Table>
+hipError_t dec_w4_launch(const Table& d, bool w_f32, hipStream_t stream) {
   const int blocks = d.begin[d.count];
   if (d.count <= 0 || blocks <= 0) return hipSuccess;
   if (w_f32)
-    hipLaunchKernelGGL(k_dec_w4<true>, dim3(static_cast<uint32_t>(blocks)), dim3(256), kDecLds, stream, d);
+    hipLaunchKernelGGL((k_dec_w4<true, Table>), dim3(static_cast<uint32_t>(blocks)), dim3(256), kDecLds, stream, d);
   else
-    hipLaunchKernelGGL(k_dec_w4<false>, dim3(static_cast<uint32_t>(blocks)), dim3(256), kDecLds, stream, d);
+    hipLaunchKernelGGL((k_dec_w4<false, Table>), dim3(static_cast<uint32_t>(blocks)), dim3(256), kDecLds, stream, d);
   return hipGetLastError();
 }
+
+template hipError_t dec_w4_launch(const DecW4Batch& d, bool w_f32, hipStream_t stream);
+template hipError_t dec_w4_launch(const DecW4Own<kDecOwn>& d, bool w_f32, hipStream_t stream);
+template hipError_t dec_w4_launch(const DecW4Own<kStepFew>& d, bool w_f32, hipStream_t stream);
 
 hipError_t ghat_w4_launch(const GhatW4Params& p, hipStream_t stream) {
   int dev = 0;
