@@ -279,14 +279,30 @@ class _DenseFn(torch.autograd.Function):
         return dx, G.to(W.dtype)
 
 
+DENSE_TILE = 256 * 256
+
+
+def dense_split(tokens, n, m):
+    """The split-K kernel forms x^T dy of an (n, m) weight.  The library's GEMM gives it
+    a few CUs and takes as long for 512 x 512 as for 1024 x 1024; split-K, with its
+    partial sums and the rounding to bf16, is the faster one from some thousand tokens
+    on (library -> split-K, us, MI355X):
+      1024 x 1024   4096 tokens 32 -> 38, 5700 45 -> 38, 8192 57 -> 44, 65536 314 -> 148
+      768 x 3072    4608 tokens 52 -> 48, 5700 68 -> 52, 8192 82 -> 61
+      2048 x 2048   4096 tokens 47 -> 59, 6144 68 -> 71, 8192 87 -> 83, 9000 101 -> 88
+      64 x 8192     4096 tokens 30 -> 22, 8192 54 -> 35, 65536 285 -> 195
+    Narrower weights than 64 and wider ones than 8192 are the library's: 4096 x 8 over
+    4096 tokens 20 -> 30, 8 x 524288 741 -> 987."""
+    if n % 8 != 0 or m % 8 != 0 or min(n, m) < 64 or max(n, m) > 8192 or n * m > 64 * DENSE_TILE:
+        return False
+    least = 4096 if min(n, m) == 64 else 5632 if n * m <= 36 * DENSE_TILE else 8704
+    return tokens >= least
+
+
 def dense(x, W):
-    """x W for 2-D x.  The library's GEMM forms x^T dy of a small weight over many
-    tokens on a few CUs (1024 x 1024, 8192 tokens: 57 us, 512 x 512: 55 us; split-K:
-    31 and 24 us with the rounding); from about 64 tiles of 256 x 256 on it fills
-    the GPU itself, and below some thousand tokens either takes about as long."""
-    n, m = W.shape
-    if (x.dim() == 2 and n % 8 == 0 and m % 8 == 0 and n * m <= 64 * 256 * 256 and x.shape[0] >= 4096
-            and (x.requires_grad or W.requires_grad) and usable(x, W)):
+    """x W for 2-D x; where split-K forms the weight's gradient, through _DenseFn."""
+    if (x.dim() == 2 and W.dim() == 2 and dense_split(x.shape[0], *W.shape) and (x.requires_grad or W.requires_grad)
+            and usable(x, W)):
         return _DenseFn.apply(x, W)
     return x @ W
 

@@ -82,3 +82,12 @@ def test_fused_norms_only_where_the_module_is_plain(monkeypatch):
                   lambda b: handle.pop().remove()) == []
     monkeypatch.setattr(blk.RMSNorm, "forward", lambda self, x: x)
     assert routes(lambda b: None) == []
+
+
+@pytest.mark.parametrize("tokens,n,m,takes", [(4096, 1024, 1024, False), (8192, 1024, 1024, True), (8192, 512, 512, True),
+                                              (4096, 2048, 2048, False), (8192, 2048, 2048, False), (16384, 2048, 2048, True),
+                                              (8192, 4096, 8, False), (8192, 8, 524288, False), (65536, 16, 8, False),
+                                              (4096, 64, 8192, True), (1 << 20, 1024, 1028, False)])
+def test_weight_gradients_that_split_k_takes(tokens, n, m, takes):
+    """Where the measurements beside the rule have it the faster one."""
+    assert ops.dense_split(tokens, n, m) == takes

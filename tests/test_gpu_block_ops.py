@@ -164,14 +164,18 @@ def test_split_qkv(b, l, heads, hd):
     assert torch.equal(qkv.grad[:, :, 1], dense[1].transpose(1, 2)) and not qkv.grad[:, :, 0::2].any()
 
 
-@pytest.mark.parametrize("rows,n,m", [(4096, 8, 16), (4096, 512, 520), (5003, 1024, 1024), (4097, 2048, 2048),
-                                      (4095, 512, 512), (4096, 2048, 2056), (4096, 12, 16)])  # the last three: the library
+@pytest.mark.parametrize("rows,n,m", [(4096, 64, 72), (4097, 2048, 64), (5632, 512, 520), (6003, 1024, 1024),
+                                      (8705, 2048, 2048), (5700, 8192, 256), (4095, 64, 64), (5631, 512, 512),
+                                      (8703, 2048, 2048), (9000, 2048, 2056), (9000, 56, 64), (9000, 64, 8200),
+                                      (6000, 68, 64)])  # the last seven: the library
 def test_dense_weight_gradient(rows, n, m):
     x, W, dy = _rand(rows, n).requires_grad_(True), _rand(n, m, seed=1), _rand(rows, m, seed=2)
     W = torch.nn.Parameter(W)
     y = ops.dense(x, W)
     assert torch.equal(y, x.detach() @ W.detach())
-    own = rows >= 4096 and n % 8 == 0 and n * m <= 2048 * 2048
+    own = (rows, n, m) in [(4096, 64, 72), (4097, 2048, 64), (5632, 512, 520), (6003, 1024, 1024), (8705, 2048, 2048),
+                           (5700, 8192, 256)]
+    assert ops.dense_split(rows, n, m) == own
     assert (type(y.grad_fn).__name__ == "_DenseFnBackward") == own
     y.backward(dy)
     assert torch.equal(x.grad, dy @ W.detach().t())
