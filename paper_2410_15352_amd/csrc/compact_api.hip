@@ -221,23 +221,33 @@ int launch_splitk_reduce(const float* part, int splits, int64_t ldp, int64_t pla
 }
 
 // The direct kernel's tiles of a group, or 0 where the split-K plan is the faster
-// one.  Direct: 4 us and 4.65 us per 1000 tokens for each round of tiles over the
-// CUs (the copies of a CU).  Split-K: 14 us (two launches and the partial sums) and
-// the longer of the operands at 4.9 TB/s and 0.75 us per K tile of a split.
-// (MI355X: gate|up of LLaMA-60M, 1000 tokens: 7 against 16 us; 8192: 40 against 24.)
+// one; in us on MI355X, over 19 shapes of 1 to 2752 tiles and 12 to 14 token counts
+// each.  Direct: 3, and for each round of tiles over the CUs 4.25 (first copies, last
+// steps, stores) and a CU's copies, 2.3 per 1000 tokens, or 3.6 where several rounds
+// follow each other.  Split-K: 10 for two launches, the outputs and the padded partial
+// sums by their bytes, and the longer of the operands at 4.9 TB/s and 0.75 per K tile
+// of a split.  (r x m, tokens; direct against split-K: 128 x 1376, 1000: 9 and 20;
+// 256 x 2752, 4096: 18 and 31; 512 x 5461, 64: 16 and 24, 3000: 47 and 40; 1500 x 3000,
+// 16: 25 and 21; 2048 x 5461, 64: 50 and 36.  Priced by its copies alone the direct
+// kernel took those last two.)  Past 4608 tokens x rounds several rounds cost more than
+// the estimate (1365 x 2048, 2048 tokens: 39 against 36); one round stays faster up to
+// 8192 tokens and more (256 x 2752: 30 against 35) but is left to split-K there.
 int64_t ghat_direct_tiles(const GhatGroupPlan& g, int64_t tokens, const int64_t* r, const int64_t* m,
                           const int64_t* ldz, const int64_t* lddy, int cus) {
   int64_t tiles = 0;
-  double bytes = 0.0;
+  double bytes = 0.0, plane = 0.0;
   for (int j = 0; j < g.count; ++j) {
     tiles += ceil_div(r[j], kGdTile) * ceil_div(m[j], kGdTile);
     bytes += 2.0 * double(tokens) * double(r[j] + m[j]);
+    plane += 4.0 * double(g.tiles_r[j]) * g.tm * double(g.tiles_m[j]) * g.tn;
     // 32-bit buffer offsets over all tokens (and the K tiles copied past the end)
     if ((tokens + 16 * kGhK) * std::max(ldz[j], lddy[j]) * 2 >= int64_t(1) << 31) return 0;
   }
-  if (tiles > 0x7FFFFFFF) return 0;
-  const double direct = 4.0 + double(ceil_div(tiles, cus)) * 4.65e-3 * double(tokens);
-  const double split = 14.0 + std::max(bytes / 4.9e6, 0.75 * double(ceil_div(g.split_len, kGhK)));
+  const int64_t rounds = ceil_div(tiles, cus);
+  if (tiles > 0x7FFFFFFF || tokens * rounds > 4608) return 0;
+  const double direct = 3.0 + 4.25 * double(rounds) + 1e-3 * double(tokens) * (rounds > 1 ? 3.6 * double(rounds) : 2.3);
+  const double split = 10.0 + 0.30e-6 * plane + 0.25e-6 * plane * g.splits +
+                       std::max(bytes / 4.9e6, 0.75 * double(ceil_div(g.split_len, kGhK)));
   return direct < split ? tiles : 0;
 }
 

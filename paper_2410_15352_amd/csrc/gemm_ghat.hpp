@@ -322,10 +322,11 @@ __device__ __forceinline__ void ghat_w4(const GhatW4Params& prm) {
 // G^ of few tokens in one launch, without partial sums in memory: one workgroup per
 // 64 x 64 tile, its four waves taking every fourth 32-token K tile with LDS stages
 // of their own (3 x 8 KB each, no barrier in the loop), their sums added in wave
-// order through LDS.  The split-K kernel and its reduction cost at least 14 us
-// (33 MB of partial sums written and read whatever the token count); here the time
-// is the copies of a CU, (64 + 64) columns of every token at about 55 KB per us:
-// 4.65 us per 1000 tokens.  gate|up of LLaMA-60M, 1000 tokens: 16 -> 7 us.
+// order through LDS.  The split-K kernel and its reduction cost at least 10 us, and
+// 15 to 30 with the partial sums they write and read (up to 33 MB whatever the token
+// count); here a round of tiles over the CUs takes about 7 us and the copies of a CU,
+// (64 + 64) columns of every token, 2.3 us per 1000 tokens.  128 x 1376, 1000 tokens:
+// 20 -> 9 us.
 //
 // LDS rows are 128 bytes here, chunk c of K row k at c ^ (4 ((k >> 1) & 1)): the 4
 // K rows x 64 bytes of a transposing read fill the 64 banks.

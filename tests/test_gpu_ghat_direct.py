@@ -24,7 +24,7 @@ def _slice(rows, cols, seed, scale):
 @pytest.mark.parametrize("T,ms,rs", [
     (1, [8], [8]), (31, [64], [64]), (33, [65], [63]), (127, [1], [1]), (129, [200, 33], [72, 65]),
     (1000, [1376, 1376], [128, 128]), (1025, [520] * 7 + [513], [40] * 8), (2047, [1030], [342]),
-    (300, [5461], [512]),
+    (300, [5461], [512]), (3001, [1376], [128]), (4096, [700], [330]), (1536, [2752], [500]),
 ])
 def test_ghat_direct(T, ms, rs):
     n = max(64, *rs)
@@ -44,3 +44,20 @@ def test_ghat_direct(T, ms, rs):
         err = np.abs(g.cpu().numpy().astype(np.float64) - ref)
         assert (err <= acc_bound(T) * (np.abs(zt) @ np.abs(d)) + U32 * np.abs(ref)).all()
         mo, ro = mo + m, ro + r
+
+
+@pytest.mark.parametrize("T,m,r,direct", [(1, 64, 16, True), (1000, 1376, 128, True), (64, 5461, 512, True),
+                                          (4096, 2752, 256, True), (3000, 5461, 512, False), (16, 3000, 1500, False),
+                                          (64, 5461, 2048, False), (1024, 3000, 1500, False), (8192, 1376, 128, False)])
+def test_rule(T, m, r, direct):
+    """The direct kernel where it was measured faster by more than a few percent."""
+    dy, z = _slice(T, m, T, 0.01), _slice(T, r, T + 1, 2.0)
+    ws = torch.empty(cp.bwd_workspace_bytes(T, r, m, r), dtype=torch.uint8, device=dev())
+    G = torch.empty(r, m, device=dev())
+    cp.compact_bwd(dy, None, z, None, G, ws=ws)
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        cp.compact_bwd(dy, None, z, None, G, ws=ws)
+        torch.cuda.synchronize()
+    names = " ".join(e.name for e in prof.events())
+    assert ("k_ghat_direct" in names) == direct and ("k_ghat_w4" in names) != direct, names
