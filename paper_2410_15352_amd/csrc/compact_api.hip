@@ -622,7 +622,7 @@ int fwd_group_w4(const void* x, int64_t ldx, const void* W, int64_t ldw, void* y
       tiled_fits(rows_b, n);
   TileKind kind = TileKind::kPersistent;
   if ((st = choose_gemm(tokens, G.msum, gather ? 0 : G.rsum, n, w4, false,
-                        gemm_tile_eligible(tokens, n, ldx, ldb, rows_b), kind)))
+                        gemm_tile_eligible(tokens, n, ldx, ldb, rows_b, ldy, gather ? 0 : ldz), kind)))
     return st;
   const bool tile = kind != TileKind::kPersistent;
   taken = ws != nullptr && (tile || w4);
@@ -911,7 +911,7 @@ int bwd_impl(const void* dy, int64_t lddy, const void* W, int64_t ldw, const voi
   const bool w4 = gemm_w4_eligible(tokens, m, lddy, ldw, n, lddx, n, 0, 0, stage_w);
   TileKind kind = TileKind::kPersistent;
   if (dx != nullptr &&
-      (st = choose_gemm(tokens, n, 0, m, w4, stage_w, gemm_tile_eligible(tokens, m, lddy, ldw, n), kind)))
+      (st = choose_gemm(tokens, n, 0, m, w4, stage_w, gemm_tile_eligible(tokens, m, lddy, ldw, n, lddx, 0), kind)))
     return st;
   if (dx != nullptr && kind != TileKind::kPersistent) {
     // a tile kernel reads W [n][m] as it is: one launch, no copy of W

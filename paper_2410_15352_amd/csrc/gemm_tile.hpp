@@ -231,8 +231,9 @@ constexpr int kTileKinds = 4;
 // tile kernels do without.
 TileKind gemm_tile_choose(int64_t M, int64_t n0, int64_t n1, int64_t K, bool persistent, bool copies, int cus);
 
-// True when the tile kernels take this product: 32-bit buffer offsets inside a tile.
-bool gemm_tile_eligible(int64_t M, int64_t K, int64_t lda, int64_t ldb, int64_t rows_b);
+// True when the tile kernels take this product: 32-bit buffer offsets inside a tile,
+// and output leading dimensions (ldc1 = 0: one segment) that W4Seg's int holds.
+bool gemm_tile_eligible(int64_t M, int64_t K, int64_t lda, int64_t ldb, int64_t rows_b, int64_t ldc0, int64_t ldc1);
 
 // Launches a tile kernel (kind != kPersistent); tiles_n, tiles, band_rows and
 // the segments' tiles are filled in here.

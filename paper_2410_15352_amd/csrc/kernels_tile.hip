@@ -124,9 +124,9 @@ TileKind gemm_tile_choose(int64_t M, int64_t n0, int64_t n1, int64_t K, bool per
   return static_cast<TileKind>(best);
 }
 
-bool gemm_tile_eligible(int64_t M, int64_t K, int64_t lda, int64_t ldb, int64_t rows_b) {
+bool gemm_tile_eligible(int64_t M, int64_t K, int64_t lda, int64_t ldb, int64_t rows_b, int64_t ldc0, int64_t ldc1) {
   const int64_t lim = int64_t(1) << 31;
-  if (M < 1 || K < 1 || M >= lim || rows_b >= lim) return false;
+  if (M < 1 || K < 1 || M >= lim || rows_b >= lim || ldc0 >= lim || ldc1 >= lim) return false;
   if (lda % 8 != 0 || ldb % 8 != 0 || lda < K || ldb < K) return false;
   // at most 256 rows of an operand per tile, and K
   return (256 * lda + K + 512) * 2 < lim && (256 * ldb + K + 512) * 2 < lim;
