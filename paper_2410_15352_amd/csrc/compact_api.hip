@@ -614,12 +614,15 @@ int fwd_group_w4(const void* x, int64_t ldx, const void* W, int64_t ldw, void* y
                  hipStream_t s, bool& taken) {
   int st;
   const int64_t ldb = pt_ld(n);
-  // gather-add z: the GEMM computes y alone and its B operand is W^T alone
-  const bool gather = proj_gather(proj);
-  const int64_t rows_b = gather ? round_up(G.msum, kW4Tile) : stacked_rows(G.msum, G.rsum);
-  const bool w4 =
-      gemm_w4_eligible(tokens, n, ldx, ldb, rows_b, ldy, G.msum, gather ? 0 : ldz, gather ? 0 : G.rsum, true) &&
-      tiled_fits(rows_b, n);
+  // gather-add z: the GEMM computes y alone and its B operand is W^T alone.  Asked of
+  // the operands and not of the kernel that is the faster one, so that one code gives
+  // z in one order of additions whatever the number of tokens
+  const int64_t rows_y = round_up(G.msum, kW4Tile);
+  const bool gather = proj_gather(proj) && tiled_fits(rows_y, n) &&
+                      gemm_w4_eligible(tokens, n, ldx, ldb, rows_y, ldy, G.msum, 0, 0, true);
+  const int64_t rows_b = gather ? rows_y : stacked_rows(G.msum, G.rsum);
+  const bool w4 = gather || (gemm_w4_eligible(tokens, n, ldx, ldb, rows_b, ldy, G.msum, ldz, G.rsum, true) &&
+                             tiled_fits(rows_b, n));
   TileKind kind = TileKind::kPersistent;
   if ((st = choose_gemm(tokens, G.msum, gather ? 0 : G.rsum, n, w4, false,
                         gemm_tile_eligible(tokens, n, ldx, ldb, rows_b, ldy, gather ? 0 : ldz), kind)))

@@ -303,19 +303,39 @@ def test_gather_nan_reaches_only_drawn_columns():
     assert np.isnan(to_np(y)[t0]).all()
 
 
-@pytest.mark.parametrize("n,use_ws", [(200, True), (512, False)])
-def test_gather_flag_ignored_off_the_persistent_path(n, use_ws):
-    # n < 320 (the fused 8-wave GEMM) or no workspace: z as without the flag
-    T, m, r, s, seed = 150, 136, 24, 8, (8 << 32) | 3
+@pytest.mark.parametrize("T,n,use_ws", [(150, 200, True), (150, 512, False), (30000, 200, True), (48000, 200, True),
+                                        (1, 319, True)])
+def test_gather_flag_ignored_off_the_persistent_path(T, n, use_ws):
+    # n < 320 (on either side of the token counts where a tile kernel and the 8-wave GEMM
+    # change places, with z's columns and without) or no workspace: z as without the flag,
+    # and a NaN of x in every column of its row, which the gather would keep to the drawn ones
+    m, r, s, seed = 136, 24, 8, (8 << 32) | 3
     x, W = fwd_inputs(T, n, m, "bf16", data_seed=n)
+    t0 = T // 2
+    x[t0, n // 3] = np.nan
     xd, Wd = to_dev(x, "bf16", ld_for(n, "bf16")), to_dev(W, "bf16", ld_for(m, "bf16"))
     y, z, y2, z2 = _bf(T, m), _bf(T, r), _bf(T, m), _bf(T, r)
     ws = workspace(cp.fwd_workspace_bytes(n, m, r, 1)) if use_ws else None
     cp.compact_fwd(xd, Wd, y, z, seed, proj=f"sparse-jl:{s}:gather", ws=ws)
     cp.compact_fwd(xd, Wd, y2, z2, seed, proj=f"sparse-jl:{s}", ws=ws)
     torch.cuda.synchronize()
+    assert torch.isnan(z[t0]).all() and not torch.isnan(z[:t0]).any() and not torch.isnan(z[t0 + 1:]).any()
     assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
     assert torch.equal(z.view(torch.int16), z2.view(torch.int16))
+
+
+@pytest.mark.parametrize("T", [150, 48000])
+def test_gather_taken_whatever_the_gemm(T):
+    # n >= 320: z by the gather where a tile kernel computes y and where the persistent one does
+    n, m, r, s, seed = 320, 136, 24, 8, (8 << 32) | 3
+    x, W = fwd_inputs(T, n, m, "bf16", data_seed=n)
+    t0, i0 = T // 2, 100
+    x[t0, i0] = np.nan
+    xd, Wd = to_dev(x, "bf16", ld_for(n, "bf16")), to_dev(W, "bf16", ld_for(m, "bf16"))
+    y, z = _bf(T, m), _bf(T, r)
+    cp.compact_fwd(xd, Wd, y, z, seed, proj=f"sparse-jl:{s}:gather", ws=workspace(cp.fwd_workspace_bytes(n, m, r, 1)))
+    drawn = sparse_jl_raw(seed, n, r, s)[i0] != 0
+    assert np.array_equal(np.isnan(to_np(z)[t0]), drawn) and drawn.any() and not drawn.all()
 
 
 @pytest.mark.parametrize("T,ms,rs,s", [(1, (64,), (13,), 2),                       # one token, odd r
