@@ -17,6 +17,7 @@ from . import _lib, bwd_workspace_bytes, compact_bwd
 _vp, _i64, _i32, _f32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_float
 RMSNORM_MAX_D = 4096
 MAX_ROWS = 1 << 24  # one workgroup of 256 threads per row at most: a launch has under 2^32 threads
+MAX_CHUNKS = (1 << 32) - 256  # of 8 elements, one per thread
 IGNORE = -100  # F.cross_entropy's default ignore_index
 
 
@@ -247,7 +248,7 @@ def _swiglu_torch(gu, f):
 
 def swiglu(gu, f):
     """silu(gu[:, :f]) * gu[:, f:]."""
-    if gu.dim() == 2 and gu.shape[1] == 2 * f and f % 8 == 0 and usable(gu):
+    if gu.dim() == 2 and gu.shape[1] == 2 * f and f % 8 == 0 and gu.numel() // 16 <= MAX_CHUNKS and usable(gu):
         return _SwigluFn.apply(gu)
     return _swiglu_torch(gu, f)
 
@@ -330,7 +331,7 @@ class _SplitQkvFn(torch.autograd.Function):
             grads = [torch.zeros_like(some) if g is None else g for g in grads]
         grads = [g.transpose(1, 2) for g in grads]
         d = heads * hd
-        if torch.is_grad_enabled() or d % 8 != 0 or not usable(*grads):
+        if torch.is_grad_enabled() or d % 8 != 0 or b * l * d // 8 > MAX_CHUNKS or not usable(*grads):
             return torch.stack(grads, 2)
         out = torch.empty(ctx.shape, dtype=grads[0].dtype, device=grads[0].device)
         _call("compact_block_join3", *(g.data_ptr() for g in grads), out.data_ptr(), b * l, d, _stream(out))

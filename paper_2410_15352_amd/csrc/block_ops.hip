@@ -23,6 +23,7 @@
 namespace compact {
 namespace {
 
+constexpr int64_t kMaxBlocks = (int64_t(1) << 24) - 1;  // of 256 threads: a launch has under 2^32 threads
 constexpr float kLog2e = 1.44269504088896340736f;
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -468,7 +469,7 @@ int compact_block_rmsnorm_bwd(const RmsNormGradArgs* a, void* stream) {
 
 int compact_block_swiglu_fwd(const uint16_t* gu, uint16_t* s, uint16_t* act, int64_t rows, int64_t f, void* stream) {
   const int64_t blocks = ceil_div(rows * (f / 8), 256);
-  if (rows < 1 || f < 8 || f % 8 != 0 || f > int64_t(1) << 30 || blocks > 0x7FFFFFFF) return -1;
+  if (rows < 1 || f < 8 || f % 8 != 0 || f > int64_t(1) << 30 || blocks > kMaxBlocks) return -1;
   hipLaunchKernelGGL(k_swiglu_fwd, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, static_cast<hipStream_t>(stream),
                      gu, s, act, rows, static_cast<int>(f / 8));
   return status();
@@ -477,7 +478,7 @@ int compact_block_swiglu_fwd(const uint16_t* gu, uint16_t* s, uint16_t* act, int
 int compact_block_swiglu_bwd(const uint16_t* gu, const uint16_t* s, const uint16_t* dact, uint16_t* dgu, int64_t rows,
                              int64_t f, void* stream) {
   const int64_t blocks = ceil_div(rows * (f / 8), 256);
-  if (rows < 1 || f < 8 || f % 8 != 0 || f > int64_t(1) << 30 || blocks > 0x7FFFFFFF) return -1;
+  if (rows < 1 || f < 8 || f % 8 != 0 || f > int64_t(1) << 30 || blocks > kMaxBlocks) return -1;
   hipLaunchKernelGGL(k_swiglu_bwd, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, static_cast<hipStream_t>(stream),
                      gu, s, dact, dgu, rows, static_cast<int>(f / 8));
   return status();
@@ -485,7 +486,7 @@ int compact_block_swiglu_bwd(const uint16_t* gu, const uint16_t* s, const uint16
 
 int compact_block_join3(const void* a, const void* b, const void* c, void* out, int64_t rows, int64_t d, void* stream) {
   const int64_t blocks = ceil_div(rows * (d / 8), 256);
-  if (rows < 1 || d < 8 || d % 8 != 0 || d > int64_t(1) << 30 || blocks > 0x7FFFFFFF) return -1;
+  if (rows < 1 || d < 8 || d % 8 != 0 || d > int64_t(1) << 30 || blocks > kMaxBlocks) return -1;
   hipLaunchKernelGGL(k_join3, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, static_cast<hipStream_t>(stream),
                      static_cast<const u32x4*>(a), static_cast<const u32x4*>(b), static_cast<const u32x4*>(c),
                      static_cast<u32x4*>(out), rows, static_cast<int>(d / 8));

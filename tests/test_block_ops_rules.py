@@ -91,3 +91,14 @@ def test_fused_norms_only_where_the_module_is_plain(monkeypatch):
 def test_weight_gradients_that_split_k_takes(tokens, n, m, takes):
     """Where the measurements beside the rule have it the faster one."""
     assert ops.dense_split(tokens, n, m) == takes
+
+
+@pytest.mark.parametrize("rows,takes", [((1 << 32) - 256, True), ((1 << 32) - 255, False), (1 << 33, False)])
+def test_swiglu_launches_have_less_than_2_32_threads(monkeypatch, rows, takes):
+    """One thread per 8 elements of the result: more than a launch can have stay torch's."""
+    seen = []
+    monkeypatch.setattr(ops, "usable", lambda *t: True)
+    monkeypatch.setattr(ops._SwigluFn, "apply", lambda gu: seen.append(True))
+    monkeypatch.setattr(ops, "_swiglu_torch", lambda gu, f: seen.append(False))
+    ops.swiglu(torch.empty(1, 16, dtype=torch.bfloat16).expand(rows, 16), 8)
+    assert seen == [takes]
