@@ -90,3 +90,38 @@ def test_f32_wide_leading_dimension():
     _check(y, x @ W, np.abs(x) @ np.abs(W), n)
     P = np.asarray(projection(5, n, r), np.float64)
     _check(z, x @ P, np.abs(x) @ np.abs(P), n, extra=4 * U32)
+
+
+def test_f32_wide_leading_dimension_backward():
+    """dL/dx and G^, overwritten and accumulated, by the plain kernel: dL/do in rows of 16 MB."""
+    T, n, m, r = 5, 40, 36, 8
+    g = np.random.default_rng(4)
+    W, dy = g.standard_normal((n, m), np.float32), g.standard_normal((T, m), np.float32)
+    z, G0 = g.standard_normal((T, r), np.float32), g.standard_normal((r, m), np.float32)
+    dx, dyd, Wd, zd = _slice(np.zeros((T, n), np.float32)), _slice(dy, 1 << 22), _slice(W), _slice(z)
+    G, G2 = torch.empty(r, m, device=dev()), torch.from_numpy(G0).to(dev())
+    cp.compact_bwd(dyd, Wd, zd, dx, G)
+    cp.compact_bwd_group(dyd, Wd, zd, None, [G2], [m], [r], accumulate=True)
+    W, dy, zt = W.astype(np.float64), dy.astype(np.float64), z.T.astype(np.float64)
+    _check(dx, dy @ W.T, np.abs(dy) @ np.abs(W.T), m)
+    _check(G, zt @ dy, np.abs(zt) @ np.abs(dy), T)
+    _check(G2, G0 + zt @ dy, np.abs(zt) @ np.abs(dy) + np.abs(G0), T, extra=U32)
+    _neighbours_untouched(dx)
+
+
+def test_f32_wide_update():
+    """m of 2^22 and a ragged rest: N's rows are too long for the MFMA kernel's offsets."""
+    n, m, r, seed = 3, (1 << 22) + 5, 2, 9 << 32
+    W = _slice(0.02 * np.random.default_rng(5).standard_normal((n, m)).astype(np.float32))
+    W0 = W.clone().double()
+    gen = torch.Generator(device=dev()).manual_seed(6)
+    G = torch.randn(r, m, generator=gen, device=dev())
+    M, V = torch.zeros(r, m, device=dev()), torch.zeros(r, m, device=dev())
+    ws = torch.empty(cp.step_workspace_bytes(n, m, r, cp.F32), dtype=torch.uint8, device=dev())
+    cp.compact_step(W, G, M, V, seed, 1, 0.01, beta1=0.0, beta2=0.0, eps=1.0, ws=ws)
+    P = torch.empty(n, r, device=dev())
+    cp.compact_projection(seed, P)
+    P, N = P.double() / r ** 0.5, G.double() / (G.double().abs() + 1.0)
+    U, mag = 0.01 * (P @ N), 0.01 * (P.abs() @ N.abs())
+    assert bool(((W.double() - (W0 - U)).abs() <= (acc_bound(r) + 8 * U32) * mag + U32 * (W0.abs() + U.abs())).all())
+    _neighbours_untouched(W)
