@@ -12,7 +12,11 @@
 // bytes.  LLaMA-350M widths, 8192 tokens, MI355X: RMSNorm with the residual forward
 // 12 us, backward 16 + 5 us, SwiGLU 33 us (5.5 TB/s) and 44 us (6.1 TB/s), the
 // gradients of q, k, v joined 16 us; the block's forward and backward 1825 -> 1094
-// us.  Cross-entropy over 32000 logits: 108 us forward alone (4.9 TB/s; one
+// us.  Wider norms (forward and backward together, 65536 rows): d = 1024 131 us, 2048
+// 249 (5.4 TB/s of the five tensors moved), 2056 321 (4.2), 4096 517 (5.2), 12, 12, 10
+// and 12 times the torch expressions' rate; from 2056 on the backward has one wave per
+// SIMD (365 registers).
+// Cross-entropy over 32000 logits: 108 us forward alone (4.9 TB/s; one
 // chunk at a time 141) and 140 us behind the GEMM that writes the logits (148),
 // backward 187 us (5.6 TB/s), against 1.9 ms for both.
 #include <hip/hip_runtime.h>

@@ -45,8 +45,10 @@ const Variant& variant_of(int kind) {
 
 // Time of a launch, in microseconds, fitted to measurements on MI355X (67 products
 // of 200 to 65000 rows, 266 to 5461 columns, K 320 to 32000; a kernel's error is 8 to
-// 10% rms, the choice on average 0.5% from the best of the five and never more than
-// 1% slower than the persistent kernel).  The tiles run in rounds of `slots` per CU,
+// 10% rms).  On 90 other products of these ranges the choice, with the margin below,
+// was on average 0.2% from the best of the five, at most 14% (12000 x 700 + 37, K 300:
+// 22.9 us, the 64 x 64 tiles 20.2) and at most 1.3% slower than the persistent kernel,
+// which is what two runs differ by.  The tiles run in rounds of `slots` per CU,
 // a last round of c tiles per CU lasting as long as its fullest CU: a 64-deep K step
 // with c tiles on a CU takes alone[c - 1] with few CUs at work and full[c - 1] with
 // all (the copies then share L2), a round `ov` more (first copies and output), the
@@ -101,8 +103,8 @@ hipError_t device_cus(int* cus) {
 }
 
 // The cheapest kernel by the measured costs; a tile kernel has to win by 6%, most
-// of the estimate's error (24040 x 317, K 1384, won by 5% on paper: 44.6 us against
-// 41.1).  Where the persistent kernel does not
+// of the estimate's error (without the margin 24040 x 317, K 1384, went to one that won
+// by 5% on paper: 44.6 us against 41.1).  Where the persistent kernel does not
 // take the shape (K < 320, mostly), the other choice is the eight-wave kernel of 256 x
 // 256 tiles: the tile kernels are faster until its tiles fill the CUs (K 300, 700 + 150
 // columns: 5000 rows, 80 tiles, 22 -> 15 us; 12000 rows, 188 tiles, 25 us either way;
