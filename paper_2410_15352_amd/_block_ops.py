@@ -73,9 +73,14 @@ def _stream(t):
 def _plain(t):
     """A tensor of its own storage: no subclass, no functorch wrapper, none of the batched
     tensors that is_grads_batched hands to a backward (in the engine's thread, where no
-    functorch level is seen)."""
-    return (type(t) in (torch.Tensor, torch.nn.Parameter) and not torch._C._functorch.is_functorch_wrapped_tensor(t)
-            and not torch._C._functorch.is_legacy_batchedtensor(t))
+    functorch level is seen).  Tensors that wrap another have no pointer to ask for."""
+    if type(t) is not torch.Tensor and type(t) is not torch.nn.Parameter:
+        return False
+    try:
+        t.data_ptr()
+    except RuntimeError:
+        return False
+    return True
 
 
 def usable(*tensors):
@@ -106,28 +111,32 @@ def norm_usable(x, g, *rest):
     return x.numel() // x.shape[-1] < MAX_ROWS and usable(x, g, *rest)
 
 
-def _grad(t):
-    """A gradient as the kernels take it."""
-    t = t if t.dtype == torch.bfloat16 else t.to(torch.bfloat16)
-    t = t.contiguous()
-    return t if t.data_ptr() % 16 == 0 else t.clone()
-
-
 def _grads(saved, *grads):
     """The gradients (None stays None) as a backward's kernel takes them, or None
     where that kernel must not run: a backward that is recorded, or batched
     (is_grads_batched), or whose saved tensors came back from a saved-tensor hook in
     another type, layout or place."""
-    if torch.is_grad_enabled() or not usable(*saved) or not all(g is None or _plain(g) for g in grads):
+    if torch.is_grad_enabled() or not usable(*saved):
         return None
-    grads = [None if g is None else _grad(g) for g in grads]
-    return grads if usable(*(g for g in grads if g is not None)) else None
+    out, dev = [], saved[0].get_device()
+    for t in grads:
+        if t is not None:
+            if not _plain(t) or t.get_device() != dev:
+                return None
+            if t.dtype != torch.bfloat16:
+                t = t.to(torch.bfloat16)
+            if not t.is_contiguous():
+                t = t.contiguous()
+            if t.data_ptr() % 16 != 0:
+                t = t.clone()
+        out.append(t)
+    return out
 
 
-def _companion(t, like, dtype, shape):
+def _companion(t, like, dtype, count):
     """A saved tensor beside the bf16 ones is still what the forward's kernel wrote or read."""
-    return (_plain(t) and t.dtype == dtype and tuple(t.shape) == tuple(shape) and t.is_contiguous()
-            and t.device == like.device)
+    return (t.dtype == dtype and t.numel() == count and _plain(t) and t.is_contiguous()
+            and t.get_device() == like.get_device())
 
 
 def _torch_grad(fn, x, dy):
@@ -178,16 +187,16 @@ class _NormFn(torch.autograd.Function):
         x, rstd, g = ctx.saved_tensors
         if dy is None:
             return dres, dres if ctx.added else None, None, None
+        d = x.shape[-1]
+        rows = x.numel() // d
         grads = None
-        if x.shape == dy.shape and g.shape == dy.shape[-1:] and _companion(rstd, x, torch.float32, dy.shape[:-1]):
+        if x.shape == dy.shape and g.numel() == d and _companion(rstd, x, torch.float32, rows):
             grads = _grads((x, g), dy, dres)
         if grads is None:
             dx, dg = rmsnorm_reference_grad(x, rstd, g, dy, ctx.eps)
             dx = dx if dres is None else dx + dres
             return dx, dx if ctx.added else None, dg, None
         dy, dres = grads
-        d = x.shape[-1]
-        rows = x.numel() // d
         need = ctx.needs_input_grad[0] or ctx.needs_input_grad[1]
         dx = torch.empty_like(x) if need else None
         dg = torch.empty_like(g)
@@ -374,8 +383,8 @@ class _CrossEntropyFn(torch.autograd.Function):
         logits, targets, lse = ctx.saved_tensors
         rows, V = ctx.size
         if (torch.is_grad_enabled() or not _plain(dloss) or not usable(logits) or logits.shape != (rows, V)
-                or not _companion(lse, logits, torch.float32, (rows + 1,))
-                or not _companion(targets, logits, torch.int64, (rows,))):
+                or not _companion(lse, logits, torch.float32, rows + 1)
+                or not _companion(targets, logits, torch.int64, rows)):
             return _torch_grad(lambda t: _cross_entropy_torch(t, targets), logits, dloss), None
         dloss = dloss.float().contiguous()
         dx = torch.empty_like(logits)
