@@ -83,15 +83,18 @@ def _plain(t):
     return True
 
 
-def usable(*tensors):
-    """Dense bf16 tensors on the current device, outside autocast and every kind of
-    tracing."""
+def _eager():
+    """Outside autocast and every kind of tracing.  Asked before any size is looked at:
+    under a tracer a comparison of sizes would be traced, or guarded, too."""
     if torch.compiler.is_compiling() or torch.jit.is_tracing() or torch._C._len_torch_dispatch_stack() > 0:
         return False
     if torch.is_autocast_enabled("cuda"):
         return False
-    if torch._C._functorch.peek_interpreter_stack() is not None or torch.autograd.forward_ad._current_level >= 0:
-        return False
+    return torch._C._functorch.peek_interpreter_stack() is None and torch.autograd.forward_ad._current_level < 0
+
+
+def _kernel_tensors(*tensors):
+    """Dense bf16 tensors on the current device."""
     dev = None
     for t in tensors:
         if not (_plain(t) and t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.numel() > 0
@@ -104,11 +107,19 @@ def usable(*tensors):
     return True
 
 
+def usable(*tensors):
+    """Dense bf16 tensors on the current device, outside autocast and every kind of
+    tracing."""
+    return _eager() and _kernel_tensors(*tensors)
+
+
 def norm_usable(x, g, *rest):
     """Rows of x with one gain per element (other gains broadcast or are refused by torch)."""
+    if not _eager():
+        return False
     if x.dim() < 1 or x.shape[-1] % 8 != 0 or not 8 <= x.shape[-1] <= RMSNORM_MAX_D or g.shape != x.shape[-1:]:
         return False
-    return x.numel() // x.shape[-1] < MAX_ROWS and usable(x, g, *rest)
+    return x.numel() // x.shape[-1] < MAX_ROWS and _kernel_tensors(x, g, *rest)
 
 
 def _grads(saved, *grads):
@@ -257,7 +268,8 @@ def _swiglu_torch(gu, f):
 
 def swiglu(gu, f):
     """silu(gu[:, :f]) * gu[:, f:]."""
-    if gu.dim() == 2 and gu.shape[1] == 2 * f and f % 8 == 0 and gu.numel() // 16 <= MAX_CHUNKS and usable(gu):
+    if (_eager() and gu.dim() == 2 and gu.shape[1] == 2 * f and f % 8 == 0 and gu.numel() // 16 <= MAX_CHUNKS
+            and _kernel_tensors(gu)):
         return _SwigluFn.apply(gu)
     return _swiglu_torch(gu, f)
 
@@ -311,8 +323,8 @@ def dense_split(tokens, n, m):
 
 def dense(x, W):
     """x W for 2-D x; where split-K forms the weight's gradient, through _DenseFn."""
-    if (x.dim() == 2 and W.dim() == 2 and dense_split(x.shape[0], *W.shape) and (x.requires_grad or W.requires_grad)
-            and usable(x, W)):
+    if (_eager() and x.dim() == 2 and W.dim() == 2 and dense_split(x.shape[0], *W.shape)
+            and (x.requires_grad or W.requires_grad) and _kernel_tensors(x, W)):
         return _DenseFn.apply(x, W)
     return x @ W
 
@@ -400,7 +412,8 @@ def _cross_entropy_torch(logits, targets):
 
 def cross_entropy(logits, targets):
     """F.cross_entropy(logits.float(), targets) for 2-D logits and class targets."""
-    if (logits.dim() == 2 and _plain(targets) and targets.dtype == torch.int64 and targets.dim() == 1
-            and targets.shape[0] == logits.shape[0] < MAX_ROWS and targets.device == logits.device and usable(logits)):
+    if (_eager() and logits.dim() == 2 and _plain(targets) and targets.dtype == torch.int64 and targets.dim() == 1
+            and targets.shape[0] == logits.shape[0] < MAX_ROWS and targets.device == logits.device
+            and _kernel_tensors(logits)):
         return _CrossEntropyFn.apply(logits, targets.contiguous())
     return _cross_entropy_torch(logits, targets)

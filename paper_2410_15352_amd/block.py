@@ -80,7 +80,7 @@ class RMSNorm(torch.nn.Module):
 
     def add(self, x, o):
         """(x + o, norm(x + o))."""
-        if x.shape == o.shape and self._plain() and ops.norm_usable(x, self.weight, o):
+        if self._plain() and ops.norm_usable(x, self.weight, o) and x.shape == o.shape:
             return ops.add_rmsnorm(x, o, self.weight, self.eps)
         s = x + o
         return s, self(s)

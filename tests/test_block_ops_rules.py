@@ -10,7 +10,7 @@ blk = pytest.importorskip("paper_2410_15352_amd.block")
                                                (12, 12, False), (4096, 4096, True), (4104, 4104, False)])
 def test_norm_takes_one_gain_per_element(monkeypatch, width, gains, takes):
     """The kernel reads `width` gains: any other number must not reach it."""
-    monkeypatch.setattr(ops, "usable", lambda *t: True)
+    monkeypatch.setattr(ops, "_kernel_tensors", lambda *t: True)
     x, g = torch.empty(3, width, dtype=torch.bfloat16), torch.ones(gains, dtype=torch.bfloat16)
     assert ops.norm_usable(x, g) == takes
     assert not ops.norm_usable(x, g.expand(2, gains))
@@ -97,8 +97,24 @@ def test_weight_gradients_that_split_k_takes(tokens, n, m, takes):
 def test_swiglu_launches_have_less_than_2_32_threads(monkeypatch, rows, takes):
     """One thread per 8 elements of the result: more than a launch can have stay torch's."""
     seen = []
-    monkeypatch.setattr(ops, "usable", lambda *t: True)
+    monkeypatch.setattr(ops, "_kernel_tensors", lambda *t: True)
     monkeypatch.setattr(ops._SwigluFn, "apply", lambda gu: seen.append(True))
     monkeypatch.setattr(ops, "_swiglu_torch", lambda gu, f: seen.append(False))
     ops.swiglu(torch.empty(1, 16, dtype=torch.bfloat16).expand(rows, 16), 8)
     assert seen == [takes]
+
+
+def test_no_size_is_compared_under_a_tracer(recwarn):
+    """A traced block has no more of the sizes' comparisons in it than the shapes it unpacks."""
+    b, x = _block_on_cpu()
+    y = b(x)
+    t = torch.jit.trace(b, (x,))
+    assert torch.equal(t(x), y)
+    assert not [w for w in recwarn if "_block_ops" in str(w.filename) or "norm_usable" in str(w.message)]
+
+
+def test_block_compiles_in_one_graph():
+    b, x = _block_on_cpu()
+    for rows in (2, 3):  # another size: guards and recompilation
+        z = torch.compile(b, backend="eager", fullgraph=True, dynamic=True)(x[:1].expand(rows, 8, 64))
+        assert torch.equal(z, b(x[:1].expand(rows, 8, 64)))
