@@ -257,3 +257,35 @@ def test_saved_tensors_from_hooks_and_batched_gradients(i):
     (b,) = torch.autograd.grad(out, x, torch.stack([dy, 2 * dy]), is_grads_batched=True)
     assert (b[0].double() - want.double()).norm() <= 8 * BF16_U * want.double().norm()
     assert (b[1].double() - 2 * want.double()).norm() <= 16 * BF16_U * want.double().norm()
+
+
+def test_under_graph_capture():
+    """Norm, SwiGLU, the split-K weight gradient and the cross-entropy with its check,
+    forward and backward, recorded once and replayed on new inputs beside eager work."""
+    T = 5700
+    norm, W = blk.RMSNorm(128), torch.nn.Parameter(_rand(128, 80, scale=0.1))
+    x, t = _rand(T, 128).requires_grad_(True), torch.randint(40, (T,), device=dev())
+
+    def step():
+        loss = ops.cross_entropy(ops.swiglu(ops.dense(norm(x), W), 40), t)
+        return [loss.detach(), *torch.autograd.grad(loss, [x, norm.weight, W])]
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for _ in range(2):
+            step()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = step()
+    for i in range(4):
+        with torch.no_grad():
+            x.copy_(_rand(T, 128, seed=10 + i))
+            t.copy_(torch.randint(40, (T,), device=dev()))
+            W.copy_(_rand(128, 80, scale=0.1, seed=20 + i))
+        want = step()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, want):
+            assert torch.equal(a, b)
