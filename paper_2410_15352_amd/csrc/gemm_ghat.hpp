@@ -50,6 +50,8 @@
 // buffers, or zero past their end) and only reach partial-sum entries the
 // reduction never reads.
 #pragma once
+#include <type_traits>
+
 #include "gemm_bf16.hpp"
 #include "gemm_w4.hpp"
 
@@ -330,7 +332,13 @@ __device__ __forceinline__ void ghat_w4(const GhatW4Params& prm) {
 //
 // LDS rows are 128 bytes here, chunk c of K row k at c ^ (4 ((k >> 1) & 1)): the 4
 // K rows x 64 bytes of a transposing read fill the 64 banks.
-constexpr int kGdTile = 64, kGdStages = 3;
+//
+// A wave's sums are folded into a second set of registers every kGdChunk K tiles, so
+// that no fp32 chain is longer than a split's: in one chain over all its tokens the
+// error against 64 bits grew past split-K's (256 x 2752, 4096 tokens: 1.9e-7 against
+// 1.2e-7; folded 0.9e-7, and below split-K from 300 to 4600 tokens, for 3 to 5% of the
+// time between 1000 and 2500).
+constexpr int kGdTile = 64, kGdStages = 3, kGdChunk = 4;
 constexpr uint32_t kGdOperand = kGhK * kGdTile * 2, kGdStage = 2 * kGdOperand;  // 4 KB, 8 KB
 constexpr size_t kGdLds = size_t(4) * kGdStages * kGdStage;                     // 96 KB
 
@@ -383,19 +391,22 @@ __device__ __forceinline__ void ghat_direct(const GhatDirectParams& prm) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(c < 4 ? rz : ry, reinterpret_cast<w4_lds_void*>(static_cast<uintptr_t>(dst)),
                                              16, static_cast<int>(vo | oob), 0, 0, 0);
   };
-  f32x16 acc[2][2];
+  f32x16 acc[2][2], sum[2][2];  // of the last kGdChunk K tiles at most, and of all before them
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+      for (int e = 0; e < 16; ++e) sum[i][j][e] = 0.0f;
 #pragma unroll
   for (int s = 0; s < kGdStages - 1; ++s)
 #pragma unroll
     for (int c = 0; c < 8; ++c) copy(wave + 4 * s, s, c);
   int st = 0;
-  for (int u = wave; u < kt; u += 4) {
+  // K tile u into acc, from zero when it is the first of a chunk
+  auto tile_step = [&](int u, auto first_) {
+    constexpr bool first = decltype(first_)::value;
+    const f32x16 zero = {};
     // this wave's copies of K tile u have landed; its reads of the stage that is
     // filled next returned before the last MFMAs
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * (kGdStages - 2)) : "memory");
@@ -417,16 +428,27 @@ __device__ __forceinline__ void ghat_direct(const GhatDirectParams& prm) {
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
       const int kk = m >> 2, i = (m >> 1) & 1, j = m & 1;
-      acc[i][j] = mfma32x32x16(fa[kk][i], fb[kk][j], acc[i][j]);
+      acc[i][j] = mfma32x32x16(fa[kk][i], fb[kk][j], first && kk == 0 ? zero : acc[i][j]);
       copy(u + 4 * (kGdStages - 1), nst, m);
     }
     st = st == kGdStages - 1 ? 0 : st + 1;
+  };
+  for (int u = wave; u < kt;) {
+    tile_step(u, std::true_type{});
+    u += 4;
+    for (int k = 1; k < kGdChunk && u < kt; ++k, u += 4) tile_step(u, std::false_type{});
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum[i][j][e] += acc[i][j][e];
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no copy may still be writing LDS
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   float* part = reinterpret_cast<float*>(lds);  // [wave][64][64]
   __syncthreads();
-  for_each_acc(acc, lane, [&](int row, int col, float v) { part[wave * 4096 + row * 64 + col] = v; });
+  for_each_acc(sum, lane, [&](int row, int col, float v) { part[wave * 4096 + row * 64 + col] = v; });
   __syncthreads();
   float* G = prm.G[li];
 #pragma unroll 4

@@ -23,7 +23,9 @@ __global__ __launch_bounds__(256, 1) void k_ghat_w4(GhatW4Params p) {
   ghat_w4<SHAPE>(p);
 }
 
-__global__ __launch_bounds__(256, 1) void k_ghat_direct(GhatDirectParams p) { ghat_direct(p); }
+// (two waves per SIMD asked for: within 256 registers the accumulators stay in the vector
+// registers, where they are folded without being moved; LDS leaves one workgroup per CU)
+__global__ __launch_bounds__(256, 2) void k_ghat_direct(GhatDirectParams p) { ghat_direct(p); }
 
 // Four workgroups per CU for bf16 W (at most 128 registers per lane), two for fp32 W.
 template <bool WF32, class Table>

@@ -61,3 +61,18 @@ def test_rule(T, m, r, direct):
         torch.cuda.synchronize()
     names = " ".join(e.name for e in prof.events())
     assert ("k_ghat_direct" in names) == direct and ("k_ghat_w4" in names) != direct, names
+
+
+def test_precision():
+    """The sums of a wave are folded every 4 K tiles.  With c = 2.4e-8, the rms rounding
+    error of an fp32 addition, and two roundings per 16-deep MFMA step, 4096 tokens in four
+    waves of 8 chunks give sqrt(8 + 4.5 + 2.25) c = 9.2e-8 (chunks, folds, waves); one chain
+    per wave gives 8 c = 1.9e-7."""
+    T, m, r = 4096, 1376, 128
+    g = torch.Generator(device=dev()).manual_seed(7)
+    dy, z = (torch.randn(T, c, generator=g, device=dev()).to(torch.bfloat16) for c in (m, r))
+    G = torch.empty(r, m, device=dev())
+    ws = torch.empty(cp.bwd_workspace_bytes(T, r, m, r), dtype=torch.uint8, device=dev())
+    cp.compact_bwd(dy, None, z, None, G, ws=ws)
+    ref = z.double().t().contiguous() @ dy.double()
+    assert (G.double() - ref).norm() / ref.norm() <= 1.2 * 9.2e-8
