@@ -89,7 +89,7 @@ def _stream(stream, ref):
         return stream
     if ref.is_cuda:
         # the handle alone: torch.cuda.current_stream builds a Stream object each time
-        return torch._C._cuda_getCurrentRawStream(ref.device.index)
+        return torch._C._cuda_getCurrentRawStream(ref.get_device())
     return torch.cuda.current_stream(ref.device).cuda_stream
 
 

@@ -67,14 +67,20 @@ def _call(name, *args):
 
 
 def _stream(t):
-    return torch._C._cuda_getCurrentRawStream(t.device.index)
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
+
+
+_TYPES = (torch.Tensor, torch.nn.Parameter)
+_is_compiling, _is_tracing, _autocast = torch.compiler.is_compiling, torch._C._is_tracing, torch.is_autocast_enabled
+_dispatch_modes, _functorch_level = torch._C._len_torch_dispatch_stack, torch._C._functorch.peek_interpreter_stack
+_forward_ad = torch.autograd.forward_ad
 
 
 def _plain(t):
     """A tensor of its own storage: no subclass, no functorch wrapper, none of the batched
     tensors that is_grads_batched hands to a backward (in the engine's thread, where no
     functorch level is seen).  Tensors that wrap another have no pointer to ask for."""
-    if type(t) is not torch.Tensor and type(t) is not torch.nn.Parameter:
+    if type(t) not in _TYPES:
         return False
     try:
         t.data_ptr()
@@ -86,24 +92,27 @@ def _plain(t):
 def _eager():
     """Outside autocast and every kind of tracing.  Asked before any size is looked at:
     under a tracer a comparison of sizes would be traced, or guarded, too."""
-    if torch.compiler.is_compiling() or torch.jit.is_tracing() or torch._C._len_torch_dispatch_stack() > 0:
-        return False
-    if torch.is_autocast_enabled("cuda"):
-        return False
-    return torch._C._functorch.peek_interpreter_stack() is None and torch.autograd.forward_ad._current_level < 0
+    return not (_is_compiling() or _is_tracing() or _dispatch_modes() > 0 or _autocast()  # (the GPU's)
+                or _functorch_level() is not None or _forward_ad._current_level >= 0)
 
 
 def _kernel_tensors(*tensors):
     """Dense bf16 tensors on the current device."""
     dev = None
     for t in tensors:
-        if not (_plain(t) and t.is_cuda and t.dtype == torch.bfloat16 and t.is_contiguous() and t.numel() > 0
-                and t.data_ptr() % 16 == 0):
+        if type(t) not in _TYPES:
             return False
-        if dev is None:
-            dev = torch._C._cuda_getDevice()
-        if t.get_device() != dev:
+        try:
+            p = t.data_ptr()  # 0: no elements
+        except RuntimeError:  # (as in _plain)
             return False
+        at = t.get_device()  # -1: the CPU
+        if p == 0 or p % 16 != 0 or at < 0 or t.dtype != torch.bfloat16 or not t.is_contiguous():
+            return False
+        if at != dev:
+            if dev is not None or at != torch._C._cuda_getDevice():
+                return False
+            dev = at
     return True
 
 
@@ -127,27 +136,26 @@ def _grads(saved, *grads):
     where that kernel must not run: a backward that is recorded, or batched
     (is_grads_batched), or whose saved tensors came back from a saved-tensor hook in
     another type, layout or place."""
-    if torch.is_grad_enabled() or not usable(*saved):
+    if torch.is_grad_enabled() or not _eager():
         return None
-    out, dev = [], saved[0].get_device()
+    given = [t for t in grads if t is not None]
+    if _kernel_tensors(*saved, *given):
+        return grads
+    if not _kernel_tensors(*saved) or not all(map(_plain, given)):
+        return None
+    out = []
     for t in grads:
         if t is not None:
-            if not _plain(t) or t.get_device() != dev:
-                return None
-            if t.dtype != torch.bfloat16:
-                t = t.to(torch.bfloat16)
-            if not t.is_contiguous():
-                t = t.contiguous()
-            if t.data_ptr() % 16 != 0:
-                t = t.clone()
+            t = t.to(torch.bfloat16).contiguous()
+            t = t if t.data_ptr() % 16 == 0 else t.clone()
         out.append(t)
-    return out
+    return out if _kernel_tensors(*(t for t in out if t is not None)) else None
 
 
-def _companion(t, like, dtype, count):
+def _companion(t, dtype, count):
     """A saved tensor beside the bf16 ones is still what the forward's kernel wrote or read."""
-    return (t.dtype == dtype and t.numel() == count and _plain(t) and t.is_contiguous()
-            and t.get_device() == like.get_device())
+    return (t.dtype == dtype and t.numel() == count and _plain(t) and t.is_cuda and t.is_contiguous()
+            and t.get_device() == torch._C._cuda_getDevice())
 
 
 def _torch_grad(fn, x, dy):
@@ -189,7 +197,7 @@ class _NormFn(torch.autograd.Function):
                                      None if add is None else total.data_ptr(), y.data_ptr(), rstd.data_ptr(), rows, d,
                                      eps)), _stream(x))
         ctx.set_materialize_grads(False)
-        ctx.added, ctx.eps = add is not None, eps
+        ctx.added, ctx.eps, ctx.size = add is not None, eps, (rows, d)
         ctx.save_for_backward(x if add is None else total, rstd, g)
         return (x if add is None else total), y
 
@@ -198,10 +206,9 @@ class _NormFn(torch.autograd.Function):
         x, rstd, g = ctx.saved_tensors
         if dy is None:
             return dres, dres if ctx.added else None, None, None
-        d = x.shape[-1]
-        rows = x.numel() // d
+        rows, d = ctx.size
         grads = None
-        if x.shape == dy.shape and g.numel() == d and _companion(rstd, x, torch.float32, rows):
+        if x.numel() == rows * d and x.size(-1) == d == g.numel() and _companion(rstd, torch.float32, rows):
             grads = _grads((x, g), dy, dres)
         if grads is None:
             dx, dg = rmsnorm_reference_grad(x, rstd, g, dy, ctx.eps)
@@ -209,7 +216,7 @@ class _NormFn(torch.autograd.Function):
             return dx, dx if ctx.added else None, dg, None
         dy, dres = grads
         need = ctx.needs_input_grad[0] or ctx.needs_input_grad[1]
-        dx = torch.empty_like(x) if need else None
+        dx = torch.empty_like(dy) if need else None
         dg = torch.empty_like(g)
         part = torch.empty(_call("compact_block_rmsnorm_parts", rows), d, dtype=torch.float32, device=x.device)
         _call("compact_block_rmsnorm_bwd",
@@ -252,7 +259,7 @@ class _SwigluFn(torch.autograd.Function):
     def backward(ctx, dact):
         gu, s = ctx.saved_tensors
         rows, f = dact.shape
-        grads = _grads((gu, s), dact) if gu.shape == (rows, 2 * f) and s.shape == dact.shape else None
+        grads = _grads((gu, s), dact) if gu.numel() == 2 * rows * f and gu.size(-1) == 2 * f and s.numel() == rows * f else None
         if grads is None:
             return _torch_grad(lambda t: _swiglu_torch(t, f), gu, dact)
         (dact,) = grads
@@ -394,9 +401,9 @@ class _CrossEntropyFn(torch.autograd.Function):
     def backward(ctx, dloss):
         logits, targets, lse = ctx.saved_tensors
         rows, V = ctx.size
-        if (torch.is_grad_enabled() or not _plain(dloss) or not usable(logits) or logits.shape != (rows, V)
-                or not _companion(lse, logits, torch.float32, rows + 1)
-                or not _companion(targets, logits, torch.int64, rows)):
+        if (torch.is_grad_enabled() or not _plain(dloss) or not usable(logits) or logits.numel() != rows * V or logits.size(-1) != V
+                or not _companion(lse, torch.float32, rows + 1)
+                or not _companion(targets, torch.int64, rows)):
             return _torch_grad(lambda t: _cross_entropy_torch(t, targets), logits, dloss), None
         dloss = dloss.float().contiguous()
         dx = torch.empty_like(logits)
